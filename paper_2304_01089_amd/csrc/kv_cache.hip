@@ -122,58 +122,88 @@ __global__ void __launch_bounds__(256) kv_quant_kernel(const uint4* x, int64_t T
   }
 }
 
+// Read-back.  Memory bound (d*bits/8 bytes in, 2d out per row), so the stores decide: a lane expands 8
+// consecutive codes of a row into one 16-byte store, a wave's store is 1 KiB contiguous, and the stores
+// are non-temporal (nothing here reads them again).  Measured at 8192 x 12288, 3 bits: one lane per 32-code
+// group, four 16-byte stores 64 bytes apart, 91 us; this split with ordinary stores 68 us; non-temporal 42 us
+// (5.7 TB/s).  The 8 positions' constants stay in registers; kKvRowsAhead rows are requested while the rows
+// before them are expanded (2, 4 and 8 rows measured the same).
+constexpr int kKvRowsAhead = 2;
+
 template <int BITS>
-__global__ void __launch_bounds__(128) kv_dequant_kernel(const uint8_t* codes, int64_t T, int32_t d, const KvPos* pos,
+__global__ void __launch_bounds__(256) kv_dequant_kernel(const uint8_t* codes, int64_t T, int32_t d, const KvPos* pos,
                                                          uint16_t* out, int32_t blocks_per_row) {
   typedef float f2 __attribute__((ext_vector_type(2)));
   typedef __bf16 b2 __attribute__((ext_vector_type(2)));
-  constexpr int GB = BITS * 4;                         // bytes of a 32-code group
-  const int groups = d / kGroup;
-  const int gi = (blockIdx.x % blocks_per_row) * 128 + threadIdx.x;       // this thread's group, the same for every row
-  if (gi >= groups) return;
-  float s[32], zf[32];
+  typedef unsigned u4v __attribute__((ext_vector_type(4)));
+  constexpr int ND = (BITS == 3) ? 3 : BITS / 4;       // dwords a lane reads per row
+  const int u = static_cast<int>(blockIdx.x % blocks_per_row) * 256 + static_cast<int>(threadIdx.x);   // unit of 8 codes, the same for every row
+  if (u >= d / 8) return;
+  float s[8], zf[8];
 #pragma unroll
-  for (int j = 0; j < 32; ++j) {
-    const KvPos kp = pos[gi * kGroup + j];
+  for (int j = 0; j < 8; ++j) {
+    const KvPos kp = pos[u * 8 + j];
     s[j] = kp.s;
     zf[j] = static_cast<float>(kp.z);
   }
   const int64_t row_bytes = static_cast<int64_t>(d) * BITS / 8;
   const int64_t stride = gridDim.x / blocks_per_row;
-  // the next row's codes are requested before this row is expanded (rows past the end: the last row again)
-  auto load_row = [&](int64_t row, uint32_t (&w)[GB / 4]) {
+  const int k3 = u & 3;                                // 3-bit: which quarter of the 32-code group
+  const uint8_t* lane_src = codes + ((BITS == 3) ? static_cast<int64_t>(u >> 2) * 12 : static_cast<int64_t>(u) * BITS);
+  uint16_t* lane_dst = out + static_cast<int64_t>(u) * 8;
+  // (rows past the end: the last row again, never stored)
+  auto load_row = [&](int64_t row, uint32_t (&w)[ND]) {
     if (row >= T) row = T - 1;
-    const uint32_t* p = reinterpret_cast<const uint32_t*>(codes + row * row_bytes + static_cast<int64_t>(gi) * GB);
-    if constexpr (BITS == 3) {
-      w[0] = p[0]; w[1] = p[1]; w[2] = p[2];
-    } else {
+    const uint32_t* p = reinterpret_cast<const uint32_t*>(lane_src + row * row_bytes);
 #pragma unroll
-      for (int k = 0; k < GB / 16; ++k) {
-        const uint4 v = reinterpret_cast<const uint4*>(p)[k];
-        w[4 * k] = v.x; w[4 * k + 1] = v.y; w[4 * k + 2] = v.z; w[4 * k + 3] = v.w;
+    for (int k = 0; k < ND; ++k) w[k] = p[k];
+  };
+  auto store_row = [&](int64_t row, const uint32_t (&w)[ND]) {
+    int q[8];
+    if constexpr (BITS == 8) {
+#pragma unroll
+      for (int j = 0; j < 8; ++j) q[j] = static_cast<int>(w[(j / 4) % ND] << (24 - 8 * (j & 3))) >> 24;
+    } else if constexpr (BITS == 4) {
+#pragma unroll
+      for (int b = 0; b < 4; ++b) {
+        q[b] = static_cast<int>(w[0] << (24 - 8 * b)) >> 28;
+        q[4 + b] = static_cast<int>(w[0] << (28 - 8 * b)) >> 28;
+      }
+    } else {
+      // quarters 0..2 hold their codes in bits 7..5 and 4..2 of their own dword's bytes; quarter 3's are
+      // spread over the three dwords and are brought into the same places
+      const uint32_t w3 = ((w[0] << 6) & 0xc0c0c0c0u) | ((w[2 % ND] << 5) & 0x20202020u) | ((w[1 % ND] << 3) & 0x18181818u) |
+                          ((w[2 % ND] << 1) & 0x04040404u);
+      const uint32_t v = k3 == 0 ? w[0] : (k3 == 1 ? w[1 % ND] : (k3 == 2 ? w[2 % ND] : w3));
+#pragma unroll
+      for (int b = 0; b < 4; ++b) {
+        q[b] = static_cast<int>(v << (24 - 8 * b)) >> 29;
+        q[4 + b] = static_cast<int>(v << (27 - 8 * b)) >> 29;
       }
     }
-  };
-  uint32_t w[GB / 4], wn[GB / 4];
-  int64_t row = blockIdx.x / blocks_per_row;
-  load_row(row, w);
-  for (; row < T; row += stride) {
-    load_row(row + stride, wn);
-    int q[32];
-    decode_group<BITS>(w, q);
-    uint32_t o[16];
+    u4v o;
 #pragma unroll
-    for (int j = 0; j < 32; j += 2) {
+    for (int j = 0; j < 8; j += 2) {
       // s (x_q - z): the integer difference is exact in fp32, one rounded product, then bf16 (ties to even)
       const f2 pr = {__fmul_rn(s[j], static_cast<float>(q[j]) - zf[j]), __fmul_rn(s[j + 1], static_cast<float>(q[j + 1]) - zf[j + 1])};
       const b2 cv = __builtin_convertvector(pr, b2);
       o[j / 2] = *reinterpret_cast<const uint32_t*>(&cv);
     }
-    uint4* dst = reinterpret_cast<uint4*>(out + row * d + static_cast<int64_t>(gi) * kGroup);
+    if (row < T) __builtin_nontemporal_store(o, reinterpret_cast<u4v*>(lane_dst + row * d));
+  };
+  uint32_t cur[kKvRowsAhead][ND], nxt[kKvRowsAhead][ND];
+  int64_t row = blockIdx.x / blocks_per_row;
 #pragma unroll
-    for (int k = 0; k < 4; ++k) dst[k] = make_uint4(o[4 * k], o[4 * k + 1], o[4 * k + 2], o[4 * k + 3]);
+  for (int k = 0; k < kKvRowsAhead; ++k) load_row(row + k * stride, cur[k]);
+  for (; row < T; row += kKvRowsAhead * stride) {
 #pragma unroll
-    for (int k = 0; k < GB / 4; ++k) w[k] = wn[k];
+    for (int k = 0; k < kKvRowsAhead; ++k) load_row(row + (kKvRowsAhead + k) * stride, nxt[k]);
+#pragma unroll
+    for (int k = 0; k < kKvRowsAhead; ++k) store_row(row + k * stride, cur[k]);
+#pragma unroll
+    for (int k = 0; k < kKvRowsAhead; ++k)
+#pragma unroll
+      for (int j = 0; j < ND; ++j) cur[k][j] = nxt[k][j];
   }
 }
 
@@ -202,12 +232,13 @@ int32_t launch_kv_dequant(const void* codes, int64_t T, int32_t d, const KvPos* 
   if (T == 0) return RPTQ_OK;
   int cus = 0;
   if (int32_t s = device_compute_units(st, &cus)) return s;
-  const int blocks_per_row = (d / kGroup + 127) / 128;
-  // (a thread's constants are 512 bytes: at least 16 rows per thread while the batch allows)
-  int64_t rows_par = (static_cast<int64_t>(cus) * 16 + blocks_per_row - 1) / blocks_per_row;
-  rows_par = std::min<int64_t>(rows_par, std::max<int64_t>((T + 15) / 16, (static_cast<int64_t>(cus) * 4 + blocks_per_row - 1) / blocks_per_row));
+  const int blocks_per_row = (d / 8 + 255) / 256;
+  // eight workgroups per compute unit, but at least eight rows per thread while that leaves two per
+  // compute unit (a thread's constants are 128 bytes, eight times a row's store)
+  int64_t rows_par = (static_cast<int64_t>(cus) * 8 + blocks_per_row - 1) / blocks_per_row;
+  rows_par = std::min<int64_t>(rows_par, std::max<int64_t>((T + 7) / 8, (static_cast<int64_t>(cus) * 2 + blocks_per_row - 1) / blocks_per_row));
   rows_par = std::min<int64_t>(std::max<int64_t>(rows_par, 1), T);
-  const dim3 grid(static_cast<unsigned>(blocks_per_row * rows_par)), block(128);
+  const dim3 grid(static_cast<unsigned>(blocks_per_row * rows_par)), block(256);
   const uint8_t* cp = static_cast<const uint8_t*>(codes);
   uint16_t* op = static_cast<uint16_t*>(out);
   if (bits == 3) hipLaunchKernelGGL(kv_dequant_kernel<3>, grid, block, 0, st, cp, T, d, pos, op, blocks_per_row);

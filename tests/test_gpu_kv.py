@@ -116,3 +116,24 @@ def test_full_width_cache_sampled(rp):
     dec = packfmt.unpack_groups(codes.view(T, -1)[torch.from_numpy(ts).cuda()].cpu().numpy(), d, bits)
     assert np.array_equal(dec, want)
     assert np.array_equal(out[torch.from_numpy(ts).cuda()].float().cpu().numpy(), kvo.kv_dequant(want, ref, 1))
+
+
+@pytest.mark.parametrize("bits", [3, 4, 8])
+@pytest.mark.parametrize("T,H,dh", [(1, 1, 32), (3, 1, 32), (9, 65, 32), (5, 3, 1024), (1041, 2, 64)])
+def test_read_back_at_tile_edges(rp, T, H, dh, bits):
+    """Rows and columns around the read-back kernel's tiles (256 units of 8 codes, rows in strides); bit for bit."""
+    rng = np.random.default_rng(T * 1000 + H + bits)
+    d, g = H * dh, 2
+    lo = -rng.random(d).astype(np.float32) - np.float32(0.1)
+    hi = rng.random(d).astype(np.float32) + np.float32(0.1)
+    ref = kvo.cluster_heads([lo], [hi], H, g, bits, 3)
+    got = rp.rptq_cluster_heads([lo], [hi], H, g, bits, 3)
+    table = torch.empty(rp.rptq_kv_table_bytes(d), dtype=torch.uint8, device="cuda")
+    rp.rptq_kv_tables(got["perm"], got["cluster_off"], got["s"][0], got["inv_s"][0], got["z"][0], d, H, g, table)
+    q = rng.integers(-(1 << (bits - 1)), 1 << (bits - 1), (T, d)).astype(np.int8)
+    packed = torch.from_numpy(packfmt.pack_groups(q, bits).reshape(-1)).cuda()
+    guard = torch.full((T * d + 512,), 7.0, dtype=torch.bfloat16, device="cuda")
+    rp.rptq_kv_dequant(packed, T, d, table, bits, guard[: T * d].view(T, d))
+    torch.cuda.synchronize()
+    assert np.array_equal(guard[: T * d].view(T, d).float().cpu().numpy(), kvo.kv_dequant(q, ref, 0))
+    assert (guard[T * d:] == 7.0).all()
