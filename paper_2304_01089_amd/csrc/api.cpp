@@ -83,9 +83,11 @@ int32_t rptq_calibrate(const void* const* x_batches, const int64_t* rows, int32_
                                        workspace, workspace_bytes, stream))
     return st;
   hipStream_t hs = static_cast<hipStream_t>(stream);
-  RPTQ_HIP(hipMemcpyAsync(ch_min, dev_min, sizeof(float) * d, hipMemcpyDeviceToHost, hs));
-  RPTQ_HIP(hipMemcpyAsync(ch_max, dev_max, sizeof(float) * d, hipMemcpyDeviceToHost, hs));
+  std::vector<float> both(2 * static_cast<size_t>(d));          // (dev_min and dev_max adjoin: one copy)
+  RPTQ_HIP(hipMemcpyAsync(both.data(), dev_min, sizeof(float) * both.size(), hipMemcpyDeviceToHost, hs));
   RPTQ_HIP(hipStreamSynchronize(hs));
+  std::memcpy(ch_min, both.data(), sizeof(float) * d);
+  std::memcpy(ch_max, both.data() + d, sizeof(float) * d);
   return cluster_channels(ch_min, ch_max, d, g, bits, seed, max_iter, assign, perm, cluster_off, s, inv_s, z, g_eff);
 }
 

@@ -3,9 +3,15 @@
 // same arithmetic as the online kernel (fp64 row sums, fp32 elementwise chain), or x
 // itself at a non-LayerNorm site, optionally through max(.,0).
 //
-// Each thread owns up to 4 chunks of 8 channels for all rows of its workgroup and keeps
-// running extrema in registers; workgroups merge through atomic min/max on an
-// order-preserving integer image of the floats, so the result does not depend on order.
+// One launch covers all batches.  A workgroup of up to 1024 threads holds several rows at a time, one
+// per thread group; each thread owns up to CH chunks of 8 channels of its group's rows and keeps running
+// extrema in registers.  The groups of a workgroup merge in LDS, the workgroups through atomic min/max
+// on an order-preserving integer image of the floats, so the result does not depend on order.
+//
+// What bounds it is the global atomics, 2d per workgroup on the same 2d words, against the depth of one
+// group's row loop: a batch of 128 rows x 2048 channels in 128 one-row workgroups took 22.6 us (and each of 16
+// batches its own launch, 362 us); all 2048 rows in one launch take 15 us with 2 rows per group (128
+// workgroups), 20 us with 4, 31 us with 8.
 #include <hip/hip_runtime.h>
 
 #include "device_common.h"
@@ -13,7 +19,14 @@
 
 namespace rptq {
 
-constexpr int kCalChunk = 4;
+constexpr int kCalBatches = 64;           // batches one launch takes (by value)
+constexpr int kCalRowsPerGroup = 2;       // rows a thread group walks (more of them beyond 512 workgroups)
+
+struct CalBatches {
+  int32_t n;
+  const uint4* x[kCalBatches];
+  int64_t end[kCalBatches];               // first row (counted over all batches) after batch b
+};
 
 __global__ void minmax_init_kernel(uint32_t* keys, int d) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
@@ -31,95 +44,139 @@ __global__ void minmax_final_kernel(const uint32_t* keys, int d, float* ch_min, 
   }
 }
 
-template <bool LN>
-__global__ void __launch_bounds__(1024) minmax_kernel(const uint4* x, int64_t rows, int d, const float* gamma,
-                                                      const float* beta, float eps, int relu, uint32_t* keys) {
+// CH: 16-byte chunks of a row per thread.  `tpr` threads (a multiple of the wave size) share a row.
+template <bool LN, int CH>
+__global__ void __launch_bounds__(1024) minmax_kernel(CalBatches cb, int d, int tpr, const float* gamma, const float* beta,
+                                                      float eps, int relu, uint32_t* keys) {
   __shared__ double red[2][2][kMaxWaves];
-  const int tid = threadIdx.x, T = blockDim.x, lane = tid & 63, wid = tid >> 6, nw = T >> 6;
+  extern __shared__ uint32_t sh_keys[];                        // [2][d], several groups only
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wid = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wpr = tpr >> 6;                                     // waves per row
+  const int grp = wid / wpr, groups = static_cast<int>(blockDim.x) / tpr;
+  const int t = tid - grp * tpr;                                // thread of its group
   const int chunks = d / 8;
+  const int64_t total = cb.end[cb.n - 1];
+  const int64_t stride = static_cast<int64_t>(gridDim.x) * groups;
 
-  float vmin[kCalChunk][8], vmax[kCalChunk][8];
+  if (groups > 1) {
+    for (int i = tid; i < d; i += blockDim.x) {
+      sh_keys[i] = 0xffffffffu;
+      sh_keys[d + i] = 0u;
+    }
+  }
+  float vmin[CH][8], vmax[CH][8];
 #pragma unroll
-  for (int c = 0; c < kCalChunk; ++c) {
+  for (int c = 0; c < CH; ++c) {
 #pragma unroll
     for (int k = 0; k < 8; ++k) {
       vmin[c][k] = __builtin_huge_valf();
       vmax[c][k] = -__builtin_huge_valf();
     }
   }
-
+  int ch_idx[CH];                                               // clamped: a surplus lane reads the last chunk again
+  bool ch_ok[CH];
+#pragma unroll
+  for (int c = 0; c < CH; ++c) {
+    ch_ok[c] = t + c * tpr < chunks;
+    ch_idx[c] = ch_ok[c] ? t + c * tpr : chunks - 1;
+  }
+  int b = 0;                                                    // batch of the row fetched last (rows only ascend)
+  uint4 nxt[CH];
+  auto fetch = [&](int64_t row) {
+    if (row >= total) row = total - 1;
+    while (row >= cb.end[b]) ++b;
+    const uint4* p = cb.x[b] + (row - (b ? cb.end[b - 1] : 0)) * chunks;
+#pragma unroll
+    for (int c = 0; c < CH; ++c) nxt[c] = p[ch_idx[c]];
+  };
+  // all groups of a workgroup run the same number of passes (they share the barrier of a pass); a group
+  // past the end repeats the last row, which changes no extremum
+  const int64_t row0 = static_cast<int64_t>(blockIdx.x) * groups;
+  constexpr bool kAhead = CH <= 2;                              // (four chunks: a second row does not fit the registers)
+  if (kAhead) fetch(row0 + grp);
   int parity = 0;
-  for (int64_t row = blockIdx.x; row < rows; row += gridDim.x, parity ^= 1) {
-    uint4 v[kCalChunk];
-    double s1 = 0.0, s2 = 0.0;
+  for (int64_t base = row0; base < total; base += stride, parity ^= 1) {
+    if (!kAhead) fetch(base + grp);
+    uint4 v[CH];
 #pragma unroll
-    for (int c = 0; c < kCalChunk; ++c) {
-      const int idx = tid + c * T;
-      if (idx < chunks) {
-        v[c] = x[row * chunks + idx];
-        if (LN) {
-          const uint32_t w[4] = {v[c].x, v[c].y, v[c].z, v[c].w};
-#pragma unroll
-          for (int k = 0; k < 4; ++k) {
-            const double lo = static_cast<double>(bf16_lo(w[k]));
-            const double hi = static_cast<double>(bf16_hi(w[k]));
-            s1 += lo;
-            s2 = fma(lo, lo, s2);
-            s1 += hi;
-            s2 = fma(hi, hi, s2);
-          }
-        }
-      }
-    }
+    for (int c = 0; c < CH; ++c) v[c] = nxt[c];
+    if (kAhead) fetch(base + stride + grp);
     float mu = 0.0f, rstd = 1.0f;
     if (LN) {
+      double s1 = 0.0, s2 = 0.0;
+#pragma unroll
+      for (int c = 0; c < CH; ++c) {
+        const uint32_t w[4] = {v[c].x, v[c].y, v[c].z, v[c].w};
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          const double lo = ch_ok[c] ? static_cast<double>(bf16_lo(w[k])) : 0.0;
+          const double hi = ch_ok[c] ? static_cast<double>(bf16_hi(w[k])) : 0.0;
+          s1 += lo;
+          s2 = fma(lo, lo, s2);
+          s1 += hi;
+          s2 = fma(hi, hi, s2);
+        }
+      }
       const double r1 = wave_sum(s1), r2 = wave_sum(s2);
       if (lane == 0) {
         red[parity][0][wid] = r1;
         red[parity][1][wid] = r2;
       }
       __syncthreads();
-      const double t1 = partials_sum(red[parity][0], nw, lane);
-      const double t2 = partials_sum(red[parity][1], nw, lane);
+      const double t1 = partials_sum(&red[parity][0][grp * wpr], wpr, lane);
+      const double t2 = partials_sum(&red[parity][1][grp * wpr], wpr, lane);
       row_stats(t1, t2, d, eps, &mu, &rstd);
     }
 #pragma unroll
-    for (int c = 0; c < kCalChunk; ++c) {
-      const int idx = tid + c * T;
-      if (idx < chunks) {
-        const uint32_t w[4] = {v[c].x, v[c].y, v[c].z, v[c].w};
-        float gam[8], bet[8];
-        if (LN) {
-          // not kept in registers: calibration runs once, the extrema need the space
-          const float4 g0 = *reinterpret_cast<const float4*>(gamma + idx * 8), g1 = *reinterpret_cast<const float4*>(gamma + idx * 8 + 4);
-          const float4 b0 = *reinterpret_cast<const float4*>(beta + idx * 8), b1 = *reinterpret_cast<const float4*>(beta + idx * 8 + 4);
-          gam[0] = g0.x; gam[1] = g0.y; gam[2] = g0.z; gam[3] = g0.w; gam[4] = g1.x; gam[5] = g1.y; gam[6] = g1.z; gam[7] = g1.w;
-          bet[0] = b0.x; bet[1] = b0.y; bet[2] = b0.z; bet[3] = b0.w; bet[4] = b1.x; bet[5] = b1.y; bet[6] = b1.z; bet[7] = b1.w;
-        }
+    for (int c = 0; c < CH; ++c) {
+      const uint32_t w[4] = {v[c].x, v[c].y, v[c].z, v[c].w};
+      float gam[8], bet[8];
+      if (LN) {
+        // not kept in registers: the extrema need the space
+        const float4* gp = reinterpret_cast<const float4*>(gamma + ch_idx[c] * 8);
+        const float4* bp = reinterpret_cast<const float4*>(beta + ch_idx[c] * 8);
+        const float4 g0 = gp[0], g1 = gp[1], b0 = bp[0], b1 = bp[1];
+        gam[0] = g0.x; gam[1] = g0.y; gam[2] = g0.z; gam[3] = g0.w; gam[4] = g1.x; gam[5] = g1.y; gam[6] = g1.z; gam[7] = g1.w;
+        bet[0] = b0.x; bet[1] = b0.y; bet[2] = b0.z; bet[3] = b0.w; bet[4] = b1.x; bet[5] = b1.y; bet[6] = b1.z; bet[7] = b1.w;
+      }
 #pragma unroll
-        for (int k = 0; k < 8; ++k) {
-          float y = (k & 1) ? bf16_hi(w[k / 2]) : bf16_lo(w[k / 2]);
-          if (LN) y = ln_chain(y, mu, rstd, gam[k], bet[k]);
-          if (relu) y = fmaxf(y, 0.0f);
-          vmin[c][k] = fminf(vmin[c][k], y);
-          vmax[c][k] = fmaxf(vmax[c][k], y);
-        }
+      for (int k = 0; k < 8; ++k) {
+        float y = (k & 1) ? bf16_hi(w[k / 2]) : bf16_lo(w[k / 2]);
+        if (LN) y = ln_chain(y, mu, rstd, gam[k], bet[k]);
+        if (relu) y = fmaxf(y, 0.0f);
+        vmin[c][k] = fminf(vmin[c][k], y);
+        vmax[c][k] = fmaxf(vmax[c][k], y);
       }
     }
   }
 
-  if (static_cast<int64_t>(blockIdx.x) < rows) {
+  if (groups > 1) {
+    __syncthreads();                                            // (a site without LayerNorm has had no barrier since the clearing)
 #pragma unroll
-    for (int c = 0; c < kCalChunk; ++c) {
-      const int idx = tid + c * T;
-      if (idx < chunks) {
+    for (int c = 0; c < CH; ++c)
+      if (ch_ok[c]) {
 #pragma unroll
         for (int k = 0; k < 8; ++k) {
-          atomicMin(&keys[idx * 8 + k], float_key(vmin[c][k]));
-          atomicMax(&keys[d + idx * 8 + k], float_key(vmax[c][k]));
+          atomicMin(&sh_keys[ch_idx[c] * 8 + k], float_key(vmin[c][k]));
+          atomicMax(&sh_keys[d + ch_idx[c] * 8 + k], float_key(vmax[c][k]));
         }
       }
+    __syncthreads();
+    for (int i = tid; i < d; i += blockDim.x) {
+      atomicMin(&keys[i], sh_keys[i]);
+      atomicMax(&keys[d + i], sh_keys[d + i]);
     }
+  } else {
+#pragma unroll
+    for (int c = 0; c < CH; ++c)
+      if (ch_ok[c]) {
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+          atomicMin(&keys[ch_idx[c] * 8 + k], float_key(vmin[c][k]));
+          atomicMax(&keys[d + ch_idx[c] * 8 + k], float_key(vmax[c][k]));
+        }
+      }
   }
 }
 
@@ -127,19 +184,36 @@ int32_t launch_channel_minmax(const void* const* x_batches, const int64_t* rows,
                               const float* gamma, const float* beta, float eps, int32_t relu,
                               float* ch_min_dev, float* ch_max_dev, uint32_t* keys, hipStream_t st) {
   const int chunks = d / 8;
-  int threads = ((chunks + kCalChunk - 1) / kCalChunk + kWave - 1) / kWave * kWave;
-  if (threads < 256) threads = std::min(256, (chunks + kWave - 1) / kWave * kWave);
-  if (threads > 1024) return RPTQ_ERR_SHAPE;
+  // one or two chunks per thread while 1024 threads hold a row so, else four (up to 32768 channels)
+  const int ch = chunks <= kWave ? 1 : (chunks <= 2048 ? 2 : 4);
+  const int tpr = ((chunks + ch - 1) / ch + kWave - 1) / kWave * kWave;
+  if (tpr > 1024) return RPTQ_ERR_SHAPE;
+  // (several groups merge in 8 bytes of LDS per channel: as many as stay inside the default 64 KiB)
+  const int groups = d <= 8064 ? 1024 / tpr : 1;
+  const size_t shmem = groups > 1 ? static_cast<size_t>(d) * 8 : 0;
   hipLaunchKernelGGL(minmax_init_kernel, dim3((d + 255) / 256), dim3(256), 0, st, keys, d);
   RPTQ_HIP(hipGetLastError());
-  for (int b = 0; b < n_batches; ++b) {
-    if (rows[b] == 0) continue;
-    const int grid = static_cast<int>(std::min<int64_t>(rows[b], 512));
-    const uint4* xb = static_cast<const uint4*>(x_batches[b]);
+  for (int b = 0; b < n_batches;) {
+    CalBatches cb = {};
+    int64_t total = 0;
+    for (; b < n_batches && cb.n < kCalBatches; ++b) {
+      if (rows[b] == 0) continue;
+      total += rows[b];
+      cb.x[cb.n] = static_cast<const uint4*>(x_batches[b]);
+      cb.end[cb.n++] = total;
+    }
+    if (total == 0) continue;
+    const int64_t per_wg = static_cast<int64_t>(groups) * kCalRowsPerGroup;
+    const dim3 grid(static_cast<unsigned>(std::min<int64_t>((total + per_wg - 1) / per_wg, 512))), block(tpr * groups);
+    auto go = [&](auto kern) { hipLaunchKernelGGL(kern, grid, block, shmem, st, cb, d, tpr, gamma, beta, eps, relu, keys); };
     if (gamma) {
-      hipLaunchKernelGGL(minmax_kernel<true>, dim3(grid), dim3(threads), 0, st, xb, rows[b], d, gamma, beta, eps, relu, keys);
+      if (ch == 1) go(minmax_kernel<true, 1>);
+      else if (ch == 2) go(minmax_kernel<true, 2>);
+      else go(minmax_kernel<true, 4>);
     } else {
-      hipLaunchKernelGGL(minmax_kernel<false>, dim3(grid), dim3(threads), 0, st, xb, rows[b], d, gamma, beta, eps, relu, keys);
+      if (ch == 1) go(minmax_kernel<false, 1>);
+      else if (ch == 2) go(minmax_kernel<false, 2>);
+      else go(minmax_kernel<false, 4>);
     }
     RPTQ_HIP(hipGetLastError());
   }
