@@ -44,47 +44,96 @@ struct ScaleTab {
   double sz[RPTQ_MAX_CLUSTERS];     // sX_i * zX_i
 };
 
-__global__ void __launch_bounds__(256) fold_weight_kernel(FoldArgs a, ClusterGeom geom, ScaleTab tab) {
-  __shared__ float red_min[4], red_max[4];
-  __shared__ float sh_inv;
-  __shared__ int32_t sh_z;
-  __shared__ int32_t sh_wsum[RPTQ_MAX_CLUSTERS];
-  const int o = blockIdx.x;
-  const int tid = threadIdx.x;
-  const int n_units = geom.k_padded / 8;
+// R output rows per workgroup (R divides 32, so they share a packed block's row band), read once, in order, into
+// LDS as fp32 and gathered from there in cluster order.
+//
+// What bounds it is memory: 4 (or 2) bytes a weight in, half a byte out.  One row per workgroup, gathered from
+// memory 4 bytes at a time and written 4 bytes at a time, took 76 us for 8192 x 2048 fp32 weights; rows staged in
+// LDS and 16-byte pieces of R neighbouring rows written together take 25 us.  A row's pitch in LDS is odd
+// in words, so that the R lanes that read one channel of R rows use R banks.
+constexpr int kFoldThreads = 512;
 
-  if (o >= a.N) {                                  // rows added by rounding N up: all-zero codes
-    for (int u = tid; u < n_units; u += blockDim.x)
-      *reinterpret_cast<uint32_t*>(a.Wq + weight_dword_offset(o, u, geom.k_padded)) = 0u;
-    return;
-  }
-  // (zW[o] carries the validated source row of output o until this workgroup overwrites it with
-  // the row's zero point: every thread reads it here, thread 0 writes behind a barrier)
-  const int64_t src_row = a.has_perm_out ? a.zW[o] : o;
-  if (src_row < 0) {                               // a pad row of the output layout: weights 0, s = 1, z = 0
-    for (int u = tid; u < n_units; u += blockDim.x)
-      *reinterpret_cast<uint32_t*>(a.Wq + weight_dword_offset(o, u, geom.k_padded)) = 0u;
-    if (tid < geom.g) a.wsum[static_cast<int64_t>(o) * geom.g + tid] = 0;
-    __syncthreads();
-    if (tid == 0) {
-      a.sW[o] = 1.0f;
-      a.zW[o] = 0;
-      a.colterm[o] = 0.0f;
-    }
-    return;
-  }
-  const uint16_t* wb = static_cast<const uint16_t*>(a.W) + src_row * geom.k;
-  const float* wf = static_cast<const float*>(a.W) + src_row * geom.k;
-  auto wval = [&](int c) -> float { return a.w_bf16 ? __uint_as_float(static_cast<uint32_t>(wb[c]) << 16) : wf[c]; };
+struct FoldLds {
+  int rows, wsum, cluster, total;                  // byte offsets, size
+};
+__host__ __device__ inline FoldLds fold_lds_layout(int r, int k, int g, int k_padded) {
+  FoldLds l;
+  l.rows = 0;
+  l.wsum = r * (k | 1) * 4;
+  l.cluster = l.wsum + r * g * 4;
+  l.total = l.cluster + (k_padded / kGroup + 15) / 16 * 16;
+  return l;
+}
 
-  // ---- Eq. 2 over the whole row ---------------------------------------------------------
+template <int R>
+__global__ void __launch_bounds__(kFoldThreads) fold_weight_kernel(FoldArgs a, ClusterGeom geom, ScaleTab tab) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  __shared__ float sh_inv[R];
+  __shared__ int32_t sh_z[R], sh_src[R];
+  const FoldLds lds = fold_lds_layout(R, geom.k, geom.g, geom.k_padded);
+  float* rows = reinterpret_cast<float*>(smem + lds.rows);
+  int32_t* sh_wsum = reinterpret_cast<int32_t*>(smem + lds.wsum);      // [R][g]
+  uint8_t* sh_cluster = smem + lds.cluster;                            // cluster of every 32-code slice
+  const int pitch = geom.k | 1;
+  const int o0 = blockIdx.x * R;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wid = __builtin_amdgcn_readfirstlane(tid >> 6);
+  constexpr int kWaves = kFoldThreads / 64;
+  constexpr int kWavesPerRow = kWaves / R;         // waves that read one row (R <= 8)
+
+  for (int sl = tid; sl < geom.k_padded / kGroup; sl += kFoldThreads) {
+    int ci = 0;
+    for (int i = 1; i < geom.g; ++i) ci += (sl * kGroup >= geom.pad_off[i]) ? 1 : 0;
+    sh_cluster[sl] = static_cast<uint8_t>(ci);
+  }
+  for (int i = tid; i < R * geom.g; i += kFoldThreads) sh_wsum[i] = 0;
+
+  // ---- read the rows, Eq. 2 over each whole row ---------------------------------------------
+  __shared__ float red_min[kWaves], red_max[kWaves];
+  const int my_row = wid / kWavesPerRow;           // each wave reads (a part of) one row
+  const int t = (wid % kWavesPerRow) * 64 + lane;
+  constexpr int kStep = kWavesPerRow * 64;
+  const int my_o = o0 + my_row;
+  // (zW[o] carries the validated source row of output o until it is overwritten with the row's zero
+  // point behind the barrier below; rows added by rounding N up and pad rows of the output layout have none)
+  const int src_row = my_o < a.N ? (a.has_perm_out ? a.zW[my_o] : my_o) : -1;
   float lo = __builtin_huge_valf(), hi = -__builtin_huge_valf();
   bool bad = false;
-  for (int c = tid; c < geom.k; c += blockDim.x) {
-    const float w = wval(c);
-    bad |= !(fabsf(w) <= 3.4028234664e38f);         // NaN or infinity (min/max would skip a NaN)
-    lo = fminf(lo, w);
-    hi = fmaxf(hi, w);
+  if (src_row >= 0) {
+    const uint16_t* wb = static_cast<const uint16_t*>(a.W) + static_cast<int64_t>(src_row) * geom.k;
+    const float* wf = static_cast<const float*>(a.W) + static_cast<int64_t>(src_row) * geom.k;
+    float* row = rows + my_row * pitch;
+    auto take = [&](int c, float w) {
+      bad |= !(fabsf(w) <= 3.4028234664e38f);      // NaN or infinity (min/max would skip a NaN)
+      lo = fminf(lo, w);
+      hi = fmaxf(hi, w);
+      row[c] = w;
+    };
+    if (geom.k % 8 == 0) {                         // whole 16-byte chunks in every row
+      if (a.w_bf16) {
+#pragma unroll 4
+        for (int c = t * 8; c < geom.k; c += kStep * 8) {
+          const uint4 v = *reinterpret_cast<const uint4*>(wb + c);
+          const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+          for (int k = 0; k < 4; ++k) {
+            take(c + 2 * k, bf16_lo(w[k]));
+            take(c + 2 * k + 1, bf16_hi(w[k]));
+          }
+        }
+      } else {
+#pragma unroll 4
+        for (int c = t * 4; c < geom.k; c += kStep * 4) {
+          const float4 v = *reinterpret_cast<const float4*>(wf + c);
+          take(c, v.x);
+          take(c + 1, v.y);
+          take(c + 2, v.z);
+          take(c + 3, v.w);
+        }
+      }
+    } else {
+      for (int c = t; c < geom.k; c += kStep) take(c, a.w_bf16 ? __uint_as_float(static_cast<uint32_t>(wb[c]) << 16) : wf[c]);
+    }
   }
   if (bad) atomicOr(&g_fold_status, 1);
 #pragma unroll
@@ -92,65 +141,88 @@ __global__ void __launch_bounds__(256) fold_weight_kernel(FoldArgs a, ClusterGeo
     lo = fminf(lo, __shfl_xor(lo, m, kWave));
     hi = fmaxf(hi, __shfl_xor(hi, m, kWave));
   }
-  if ((tid & 63) == 0) {
-    red_min[tid >> 6] = lo;
-    red_max[tid >> 6] = hi;
-  }
-  if (tid < geom.g) sh_wsum[tid] = 0;
-  __syncthreads();
-  if (tid == 0) {
-    const double l = fminf(fminf(red_min[0], red_min[1]), fminf(red_min[2], red_min[3])) + 0.0f;
-    const double h = fmaxf(fmaxf(red_max[0], red_max[1]), fmaxf(red_max[2], red_max[3])) + 0.0f;
-    double s64, zz;
-    if (h == l) {
-      s64 = 1.0;
-      zz = -rint(l);
-    } else {
-      s64 = (h - l) / 16.0;
-      zz = -rint((h + l) / (2.0 * s64));
-    }
-    const float s32 = static_cast<float>(s64);
-    if (!(s32 >= 1.17549435e-38f && s32 <= 3.4028234664e38f)) atomicOr(&g_fold_status, 2);
-    sh_inv = static_cast<float>(1.0 / static_cast<double>(s32));
-    sh_z = static_cast<int32_t>(zz);
-    a.sW[o] = s32;
-    a.zW[o] = sh_z;
+  if (lane == 0) {
+    red_min[wid] = lo;
+    red_max[wid] = hi;
   }
   __syncthreads();
-  const float inv = sh_inv;
-  const float zf = static_cast<float>(sh_z);
-
-  // ---- Eq. 1 per weight, pack eight codes per dword ----------------------------------------
-  for (int u = tid; u < n_units; u += blockDim.x) {
-    int q[8];
-    int sum = 0;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      const int c = a.perm_pad[u * 8 + e];
-      int code = 0;
-      if (c >= 0) {
-        const float r = __fmul_rn(wval(c), inv);
-        float b = __fadd_rn(rintf(r), zf);
-        b = fminf(fmaxf(b, -8.0f), 7.0f);
-        code = static_cast<int>(b);
+  if (t == 0) {                                    // one thread per row
+    float s32 = 1.0f;
+    int32_t z32 = 0;
+    if (src_row >= 0) {
+      for (int k = 0; k < kWavesPerRow; ++k) {
+        lo = fminf(lo, red_min[wid + k]);
+        hi = fmaxf(hi, red_max[wid + k]);
       }
-      q[e] = code;
-      sum += code;
+      const double l = lo + 0.0f;
+      const double h = hi + 0.0f;
+      double s64, zz;
+      if (h == l) {
+        s64 = 1.0;
+        zz = -rint(l);
+      } else {
+        s64 = (h - l) / 16.0;
+        zz = -rint((h + l) / (2.0 * s64));
+      }
+      s32 = static_cast<float>(s64);
+      if (!(s32 >= 1.17549435e-38f && s32 <= 3.4028234664e38f)) atomicOr(&g_fold_status, 2);
+      z32 = static_cast<int32_t>(zz);
     }
-    uint32_t word = 0;
-#pragma unroll
-    for (int b = 0; b < 4; ++b) word |= static_cast<uint32_t>(((q[b] & 15) << 4) | (q[4 + b] & 15)) << (8 * b);
-    *reinterpret_cast<uint32_t*>(a.Wq + weight_dword_offset(o, u, geom.k_padded)) = word;
-    int ci = 0;
-    for (int i = 1; i < geom.g; ++i) ci += (u * 8 >= geom.pad_off[i]) ? 1 : 0;
-    atomicAdd(&sh_wsum[ci], sum);
+    sh_inv[my_row] = static_cast<float>(1.0 / static_cast<double>(s32));
+    sh_z[my_row] = z32;
+    sh_src[my_row] = src_row;
+    if (my_o < a.N) {                              // (a pad row: weights 0, s = 1, z = 0)
+      a.sW[my_o] = s32;
+      a.zW[my_o] = z32;
+    }
   }
   __syncthreads();
-  if (tid < geom.g) a.wsum[static_cast<int64_t>(o) * geom.g + tid] = sh_wsum[tid];
-  if (tid == 0) {
+
+  // ---- Eq. 1 per weight, pack: a thread owns a 16-byte piece of a packed block (two runs of 16 codes, in
+  // neighbouring slices) of one row; neighbouring threads own the same piece of neighbouring rows
+  const int r = tid % R;
+  const int src = sh_src[r];
+  const float inv = sh_inv[r];
+  const float zf = static_cast<float>(sh_z[r]);
+  const float* row = rows + r * pitch;
+  const int pieces = geom.k_padded / kGroup;
+  for (int p = tid / R; p < pieces; p += kFoldThreads / R) {
+    const int sl = (p >> 1) * 2, h = p & 1;        // first slice of the pair; which half of its codes
+    uint32_t word[4] = {0u, 0u, 0u, 0u};
+    if (src >= 0) {
+#pragma unroll
+      for (int q = 0; q < 2; ++q) {
+        int sum = 0;
+#pragma unroll
+        for (int v = 0; v < 2; ++v) {
+          const int pos = (sl + q) * kGroup + h * 16 + v * 8;
+          const int4 c0 = *reinterpret_cast<const int4*>(a.perm_pad + pos);
+          const int4 c1 = *reinterpret_cast<const int4*>(a.perm_pad + pos + 4);
+          const int c[8] = {c0.x, c0.y, c0.z, c0.w, c1.x, c1.y, c1.z, c1.w};
+#pragma unroll
+          for (int e = 0; e < 8; ++e) {
+            float b = __fadd_rn(rintf(__fmul_rn(row[c[e] < 0 ? 0 : c[e]], inv)), zf);
+            b = fminf(fmaxf(b, -8.0f), 7.0f);
+            const int code = c[e] < 0 ? 0 : static_cast<int>(b);
+            sum += code;
+            word[q * 2 + v] |= static_cast<uint32_t>(code & 15) << (8 * (e & 3) + (e < 4 ? 4 : 0));
+          }
+        }
+        atomicAdd(&sh_wsum[r * geom.g + sh_cluster[sl + q]], sum);
+      }
+    }
+    *reinterpret_cast<uint4*>(a.Wq + weight_dword_offset(o0 + r, sl * 4 + h * 2, geom.k_padded)) =
+        make_uint4(word[0], word[1], word[2], word[3]);
+  }
+  __syncthreads();
+  for (int i = tid; i < R * geom.g; i += kFoldThreads) {
+    const int o = o0 + i / geom.g;
+    if (o < a.N) a.wsum[static_cast<int64_t>(o0) * geom.g + i] = sh_wsum[i];
+  }
+  if (tid < R && o0 + tid < a.N) {
     double acc = 0.0;
-    for (int i = 0; i < geom.g; ++i) acc += tab.sz[i] * static_cast<double>(sh_wsum[i]);
-    a.colterm[o] = static_cast<float>(acc);
+    for (int i = 0; i < geom.g; ++i) acc += tab.sz[i] * static_cast<double>(sh_wsum[tid * geom.g + i]);
+    a.colterm[o0 + tid] = static_cast<float>(acc);
   }
 }
 
@@ -317,6 +389,17 @@ __global__ void unpack_weights_kernel(const uint8_t* Wq, int N, ClusterGeom geom
   }
 }
 
+template <int R>
+static int32_t launch_fold_rows(const FoldArgs& a, const ClusterGeom& geom, const ScaleTab& tab, hipStream_t st) {
+  const size_t shmem = static_cast<size_t>(fold_lds_layout(R, geom.k, geom.g, geom.k_padded).total);
+  auto kern = fold_weight_kernel<R>;
+  static LdsGrant lds_granted;
+  if (int32_t s = ensure_dynamic_lds(reinterpret_cast<const void*>(kern), shmem + 1024, &lds_granted, st)) return s;
+  hipLaunchKernelGGL(kern, dim3(a.n_padded / R), dim3(kFoldThreads), shmem, st, a, geom, tab);
+  RPTQ_HIP(hipGetLastError());
+  return RPTQ_OK;
+}
+
 int32_t launch_fold(const float* gamma, const float* beta, const int32_t* perm_pad_host, const ClusterGeom& geom,
                     const float* sX, const int32_t* zX, const void* W, int32_t w_dtype, int32_t N,
                     const int32_t* perm_out_host, int32_t* perm_pad, float* gamma_pad, float* beta_pad,
@@ -351,8 +434,16 @@ int32_t launch_fold(const float* gamma, const float* beta, const int32_t* perm_p
     tab.sz[i] = i < geom.g ? static_cast<double>(sX[i]) * static_cast<double>(zX[i]) : 0.0;
   hipLaunchKernelGGL(fold_status_clear_kernel, dim3(1), dim3(1), 0, st);
   RPTQ_HIP(hipGetLastError());
-  hipLaunchKernelGGL(fold_weight_kernel, dim3(a.n_padded), dim3(256), 0, st, a, geom, tab);
-  RPTQ_HIP(hipGetLastError());
+  // As many rows per workgroup as leave two workgroups per compute unit (eight at most: their pieces fill whole
+  // cache lines), down to one row, for which the LDS holds every width.
+  auto fits = [&](int r) { return fold_lds_layout(r, geom.k, geom.g, geom.k_padded).total <= 80 * 1024 - 256; };
+  static_assert(RPTQ_MAX_CHANNELS * 4 + RPTQ_MAX_CLUSTERS * 4 + RPTQ_MAX_K_PADDED / kGroup + 1024 <= 160 * 1024, "one row fits");
+  int32_t rc;
+  if (fits(8)) rc = launch_fold_rows<8>(a, geom, tab, st);
+  else if (fits(4)) rc = launch_fold_rows<4>(a, geom, tab, st);
+  else if (fits(2)) rc = launch_fold_rows<2>(a, geom, tab, st);
+  else rc = launch_fold_rows<1>(a, geom, tab, st);
+  if (rc) return rc;
   int32_t status = 0;
   RPTQ_HIP(hipMemcpyFromSymbolAsync(&status, HIP_SYMBOL(g_fold_status), sizeof(status), 0, hipMemcpyDeviceToHost, st));
   RPTQ_HIP(hipStreamSynchronize(st));
