@@ -24,33 +24,6 @@
 
 namespace rptq {
 
-// 16 bytes of 4-bit codes (32 codes) -> 32 int8 values (code << 4), natural order.
-__device__ __forceinline__ void unpack4(const uint4 p, uint4* lo, uint4* hi) {
-  lo->x = p.x & 0xf0f0f0f0u;
-  lo->y = (p.x << 4) & 0xf0f0f0f0u;
-  lo->z = p.y & 0xf0f0f0f0u;
-  lo->w = (p.y << 4) & 0xf0f0f0f0u;
-  hi->x = p.z & 0xf0f0f0f0u;
-  hi->y = (p.z << 4) & 0xf0f0f0f0u;
-  hi->z = p.w & 0xf0f0f0f0u;
-  hi->w = (p.w << 4) & 0xf0f0f0f0u;
-}
-
-// 12 bytes of 3-bit codes (32 codes) -> 32 int8 values (code << 5), natural order.
-__device__ __forceinline__ void unpack3(uint32_t x0, uint32_t x1, uint32_t x2, uint4* lo, uint4* hi) {
-  lo->x = x0 & 0xe0e0e0e0u;
-  lo->y = (x0 << 3) & 0xe0e0e0e0u;
-  lo->z = x1 & 0xe0e0e0e0u;
-  lo->w = (x1 << 3) & 0xe0e0e0e0u;
-  hi->x = x2 & 0xe0e0e0e0u;
-  hi->y = (x2 << 3) & 0xe0e0e0e0u;
-  hi->z = ((x0 << 6) & 0xc0c0c0c0u) | ((x2 << 5) & 0x20202020u);
-  hi->w = ((x1 << 6) & 0xc0c0c0c0u) | ((x2 << 4) & 0x20202020u);
-}
-
-// OUT: what the output stage writes - kOutBf16 / kOutF32: Y; 3, 4 or 8: the next site's packed
-// codes of that many bits (ReLU optional) and the partial row sums its product needs.
-constexpr int kOutBf16 = 0, kOutF32 = 1;
 // CWISE: the weights carry one (s, z) per (output channel, input cluster), as App. A.4 prints the
 // scheme: the rescale of a finished cluster multiplies every output column by its own
 // sX_i sW[o,i] (a table of the tile's columns in LDS), and the zero-point cross term
@@ -654,22 +627,32 @@ __global__ void __launch_bounds__(256, 2) cluster_gemm_kernel(GemmArgs a, GemmTa
   }
 }
 
-// Sum over the column tiles, in tile order, of the row sums the quantizing output stage left.
-__global__ void __launch_bounds__(64) rowterm_reduce_kernel(const double* part, int tiles_n, int64_t M, float* rowterm) {
-  const int64_t t = static_cast<int64_t>(blockIdx.x) * 64 + threadIdx.x;
-  if (t >= M) return;
-  // sixteen independent loads in flight, added in tile order (a thread per row has little else to hide latency with)
+// Sum over the column tiles of the row sums the quantizing output stage left: 16 rows per workgroup, 16
+// threads per row, each adding every 16th tile in tile order; the 16 sums are added in order.  (One thread per
+// row is a serial chain of loads: 5.5 us for 166 tiles x 32 rows against 3 us.)
+__global__ void __launch_bounds__(256) rowterm_reduce_kernel(const double* part, int tiles_n, int64_t M, float* rowterm) {
+  __shared__ double sums[16][17];
+  const int r = threadIdx.x & 15, j0 = threadIdx.x >> 4;
+  const int64_t t = static_cast<int64_t>(blockIdx.x) * 16 + r;
+  const int64_t tt = t < M ? t : M - 1;
   double acc = 0.0;
-  int j = 0;
-  for (; j + 16 <= tiles_n; j += 16) {
-    double v[16];
+  int j = j0;
+  for (; j + 48 < tiles_n; j += 64) {                        // four independent loads in flight
+    double v[4];
 #pragma unroll
-    for (int k = 0; k < 16; ++k) v[k] = part[static_cast<int64_t>(j + k) * M + t];
+    for (int k = 0; k < 4; ++k) v[k] = part[static_cast<int64_t>(j + 16 * k) * M + tt];
 #pragma unroll
-    for (int k = 0; k < 16; ++k) acc += v[k];
+    for (int k = 0; k < 4; ++k) acc += v[k];
   }
-  for (; j < tiles_n; ++j) acc += part[static_cast<int64_t>(j) * M + t];
-  rowterm[t] = static_cast<float>(acc);
+  for (; j < tiles_n; j += 16) acc += part[static_cast<int64_t>(j) * M + tt];
+  sums[j0][r] = acc;
+  __syncthreads();
+  if (j0 == 0 && t < M) {
+    double s = 0.0;
+#pragma unroll
+    for (int k = 0; k < 16; ++k) s += sums[k][r];
+    rowterm[t] = static_cast<float>(s);
+  }
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -697,7 +680,7 @@ static int32_t launch_cfg(const GemmArgs& a, const GemmTab& tab, const GemmQuant
   hipLaunchKernelGGL(kern, grid, dim3(256), shmem, st, b, tab, qo);
   RPTQ_HIP(hipGetLastError());
   if (OUT >= 2) {
-    hipLaunchKernelGGL(rowterm_reduce_kernel, dim3(static_cast<unsigned>((a.M + 63) / 64)), dim3(64), 0, st,
+    hipLaunchKernelGGL(rowterm_reduce_kernel, dim3(static_cast<unsigned>((a.M + 15) / 16)), dim3(256), 0, st,
                        qo.rt_part, b.tiles_n, a.M, q_rowterm);
     RPTQ_HIP(hipGetLastError());
   }
@@ -812,6 +795,7 @@ int32_t launch_gemm(const void* codes, int64_t M, int32_t bits, const void* Wq, 
     qo = *quant_out;
     out_mode = qo.row_bytes * 8 / N;                        // bits of the codes written
   }
+  if (cw == nullptr && small_gemm_serves(M, N, geom.g, out_mode)) return launch_small_gemm(a, tab, bits, out_mode, st);
   if (bits == 3) return launch_bits<3>(a, tab, out_mode, qo, q_rowterm, st);
   if (bits == 4) return launch_bits<4>(a, tab, out_mode, qo, q_rowterm, st);
   return launch_bits<8>(a, tab, out_mode, qo, q_rowterm, st);

@@ -1,0 +1,64 @@
+"""The product with K split over a workgroup's waves (few output tiles) against the integer form in float64, at the
+edges of its tiles and of its rule: fewer K steps than waves, clusters that end inside and at the ends of the waves'
+ranges, one cluster and 64, odd row and column counts, each of the three splits and the last shape before each."""
+import numpy as np
+import pytest
+
+import packfmt
+
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+
+
+@pytest.mark.parametrize("bits", [3, 4, 8])
+@pytest.mark.parametrize("M,N,d,g", [
+    (1, 1, 8, 8), (1, 33, 40, 9), (31, 1000, 1000, 8), (33, 70, 3000, 64), (32, 8192, 520, 13),     # 32 x 32, K in 8
+    (33, 4097, 264, 8), (100, 4097, 1032, 32), (32, 32768, 136, 10),                                # 32 x 32, K in 4
+    (64, 32736, 72, 8), (333, 4099, 1000, 16), (1000, 2048, 2056, 11),                              # 32 x 64, K in 4
+    (33, 70, 600, 7),                                                                               # too few clusters: not split
+])
+def test_split_product_against_float64(M, N, d, g, bits):
+    import paper_2304_01089_amd as rp
+    rng = np.random.default_rng(M * 7 + N + d + bits)
+    cuts = np.sort(rng.choice(np.arange(1, d), g - 1, replace=False)) if g > 1 else []
+    off = np.concatenate([[0], cuts, [d]]).astype(np.int32)
+    s = np.exp(rng.normal(-3, 1, g)).astype(np.float32)
+    z = rng.integers(-(1 << (bits - 1)), 1 << (bits - 1), g).astype(np.int32)
+    q = rng.integers(-(1 << (bits - 1)), 1 << (bits - 1), (M, d)).astype(np.int8)
+    kp = rp.rptq_padded_k(off)
+    dev = dict(device="cuda")
+    W = torch.from_numpy((0.02 * rng.standard_normal((N, d))).astype(np.float32)).cuda()
+    perm_pad = torch.zeros(kp, dtype=torch.int32, **dev)
+    Wq = torch.zeros(rp.rptq_weight_bytes(N, kp), dtype=torch.uint8, **dev)
+    sW, ct = torch.zeros(N, **dev), torch.zeros(N, **dev)
+    zW, wsum = torch.zeros(N, dtype=torch.int32, **dev), torch.zeros((N, g), dtype=torch.int32, **dev)
+    rp.rptq_fold_reorder(None, None, d, rng.permutation(d).astype(np.int32), off, s, z, W, N, d, None, perm_pad, None, None,
+                         Wq, sW, zW, wsum, ct)
+    wq = torch.empty((N, d), dtype=torch.int8, **dev)
+    rp.rptq_unpack_weights(Wq, N, off, wq)
+    codes = torch.from_numpy(packfmt.pack_codes(q, off, bits)).cuda()
+    rt = torch.from_numpy(rng.standard_normal(M).astype(np.float32)).cuda()
+    y32 = torch.full((M + 2, N), 7.0, dtype=torch.float32, **dev)
+    y16 = torch.full((M + 2, N), 7.0, dtype=torch.bfloat16, **dev)
+    for y in (y32, y16):
+        rp.rptq_cluster_gemm(codes, M, bits, Wq, N, off, s, sW, zW, ct, rt, y[:M])
+    torch.cuda.synchronize()
+    w64, q64 = wq.cpu().numpy().astype(np.float64), q.astype(np.float64)
+    total, size = np.zeros((M, N)), np.zeros((M, N))
+    pos = np.concatenate([[0], np.cumsum((np.diff(off) + 31) // 32 * 32)])       # padded start of every cluster
+    for i in range(g):
+        col = pos[i] + np.arange(off[i + 1] - off[i])
+        for step in np.unique(col // 128):                # (a cluster is split at multiples of 128 padded positions)
+            c = off[i] + np.flatnonzero(col // 128 == step)
+            P = float(s[i]) * (q64[:, c] @ w64[:, c].T)
+            total += P
+            size += np.abs(P)
+    f = lambda t: t.cpu().numpy().astype(np.float64)
+    ref = f(sW) * ((total - f(ct)) - f(zW) * f(rt)[:, None])
+    # one fp32 rounding per cluster (or part of one) in a wave's running sum, whose parts' magnitudes add up to at most
+    # `size`; one rounding of the result (twice its half unit: the fp64 terms before it carry a rounding too)
+    tol = 2.0 ** -24 * (f(sW) * (g + 8) * size + 2 * np.abs(ref)) + 1e-30
+    got = f(y32[:M])
+    assert (np.abs(got - ref) <= tol).all()
+    assert torch.equal(y16[:M], y32[:M].bfloat16())           # the same value, rounded once more
+    assert (y32[M:] == 7.0).all() and (y16[M:] == 7.0).all()
