@@ -300,12 +300,13 @@ static int32_t launch_small_cfg(const GemmArgs& a, const GemmTab& tab, hipStream
   return RPTQ_OK;
 }
 
-// Which split serves a product, by its number of 32 x 32 output tiles (T).  Measured, us, prefill / decode kernel
-// first, then 32 x 32 with K in 8, in 4, 32 x 64 with K in 4:
+// Which split serves a product, by its number of 32 x 32 output tiles (T).  Measured, us: the best tile of the prefill /
+// decode kernel first, then 32 x 32 with K in 8, in 4, 32 x 64 with K in 4:
 //     1 x  8192 x  2048 (T =  256):  8.6   5.8   6.1   8.4      128 x 3072 x  768 (T =  384):  9.7   5.8   5.1   6.6
 //    32 x  5120 x 12288 (T =  160): 28.8  12.1  15.4  19.9       32 x 20480 x 5120 (T =  640): 17.0  18.7  15.4  18.4
-//    64 x  2048 x  2048 (T =  128): 16.5   5.7   5.9   8.4      200 x 5120 x 5120 (T = 1120): 33.5  25.7  21.8  21.5
-//   333 x  4099 x  4072 (T = 1419): 33.5  29.0  24.5  21.4      512 x 8192 x 2048 (T = 4096): 20.0  45.4  30.3  31.0
+//    64 x  2048 x  2048 (T =  128): 16.5   5.7   5.9   8.4       64 x 16000 x 5120 (T = 1000): 22.4        18.7
+//   200 x  5120 x  5120 (T = 1120): 22.6  25.7  21.8  21.4      333 x 4099 x 4072 (T = 1419): 23.5  29.0  24.5  21.2
+//   512 x  3000 x  2048 (T = 1504): 12.8              13.7      512 x 4096 x 5120 (T = 2048): 24.0              28.2
 //    16 x 49152 x 12288 (T = 1536): 55.8  74.5  72.6  61.2  (decode kernel: it streams the weights at the rate of memory)
 // A cluster that is split between waves is rounded once per part.  With at least as many clusters as K ranges the sums in
 // fp64 more than make up for that (figures above); with fewer, the parts can be larger than their sum: not split.
@@ -316,7 +317,7 @@ static SmallSplit small_split(int64_t M, int32_t N, int32_t g) {
   const int64_t tiles = (M + 31) / 32 * ((N + 31) / 32);
   if (tiles <= 256) return kSplit32x32k8;
   if (tiles <= 1024) return kSplit32x32k4;
-  if (tiles <= 2048 && M > 32) return kSplit32x64k4;
+  if (tiles <= 1440 && M > 32) return kSplit32x64k4;
   return kSplitNone;
 }
 

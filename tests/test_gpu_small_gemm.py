@@ -1,5 +1,5 @@
 """The product with K split over a workgroup's waves (few output tiles) against the integer form in float64, at the
-edges of its tiles and of its rule: fewer K steps than waves, clusters that end inside and at the ends of the waves'
+edges of its tiles and of its rule (and just past it): fewer K steps than waves, clusters that end inside and at the ends of the waves'
 ranges, one cluster and 64, odd row and column counts, each of the three splits and the last shape before each."""
 import numpy as np
 import pytest
@@ -14,7 +14,8 @@ torch = pytest.importorskip("torch")
 @pytest.mark.parametrize("M,N,d,g", [
     (1, 1, 8, 8), (1, 33, 40, 9), (31, 1000, 1000, 8), (33, 70, 3000, 64), (32, 8192, 520, 13),     # 32 x 32, K in 8
     (33, 4097, 264, 8), (100, 4097, 1032, 32), (32, 32768, 136, 10),                                # 32 x 32, K in 4
-    (64, 32736, 72, 8), (333, 4099, 1000, 16), (1000, 2048, 2056, 11),                              # 32 x 64, K in 4
+    (64, 23040, 72, 8), (333, 4099, 1000, 16), (700, 2047, 2056, 11),                               # 32 x 64, K in 4
+    (65, 15400, 520, 16), (1000, 2049, 1000, 8), (2100, 4500, 200, 9),                              # not split, 64 x 128 tiles
     (33, 70, 600, 7),                                                                               # too few clusters: not split
 ])
 def test_split_product_against_float64(M, N, d, g, bits):
@@ -56,8 +57,9 @@ def test_split_product_against_float64(M, N, d, g, bits):
     f = lambda t: t.cpu().numpy().astype(np.float64)
     ref = f(sW) * ((total - f(ct)) - f(zW) * f(rt)[:, None])
     # one fp32 rounding per cluster (or part of one) in a wave's running sum, whose parts' magnitudes add up to at most
-    # `size`; one rounding of the result (twice its half unit: the fp64 terms before it carry a rounding too)
-    tol = 2.0 ** -24 * (f(sW) * (g + 8) * size + 2 * np.abs(ref)) + 1e-30
+    # `size`; one rounding of each of the two differences and of the products (the unsplit kernel forms them in fp32)
+    terms = size + np.abs(f(ct)) + np.abs(f(zW) * f(rt)[:, None])
+    tol = 2.0 ** -24 * (f(sW) * ((g + 8) * size + 4 * terms) + 2 * np.abs(ref)) + 1e-30
     got = f(y32[:M])
     assert (np.abs(got - ref) <= tol).all()
     assert torch.equal(y16[:M], y32[:M].bfloat16())           # the same value, rounded once more
