@@ -28,7 +28,8 @@ constexpr int kSmallPad = 32;              // bytes added to a slice's LDS strid
 // few times only, so the code's own way through the instruction cache counts.  (The rescale of a finished cluster exists
 // once per slice.  Four steps per pass with as many register sets of weights in flight and two LDS stages took 34.8 us
 // where this takes 30.3, at 512 x 8192 x 2048, and 17.9 against 15.4 at 32 x 20480 x 5120.)
-// Latency is covered by several waves per SIMD instead.
+// Latency is covered by several waves per SIMD instead.  (The second launch bound keeps the accumulators out of the
+// AGPRs, where a rescale costs a move per element.)
 template <int BITS, int WM, int WN, int WGN, int KS, int S, int OUT>
 __global__ void __launch_bounds__(WGN * KS * 64, WM * WN == 1 ? 4 : 2) small_gemm_kernel(GemmArgs a, GemmTab tab) {
   constexpr bool YF32 = OUT == kOutF32;
@@ -37,7 +38,7 @@ __global__ void __launch_bounds__(WGN * KS * 64, WM * WN == 1 ? 4 : 2) small_gem
   constexpr int BN = WGN * WN * 32;
   constexpr int A_SLICE = 2 * BM * 16 + kSmallPad;       // [half][row][16 B]
   constexpr int A_STAGE = S * A_SLICE;
-  constexpr int A_PER = BM * S / 64;          // (row, slice) units per lane and K step
+  constexpr int A_PER = BM * S / 64;                     // (row, slice) units per lane and K step
   constexpr int GB = ActFmt<BITS>::kGroupBytes;
   constexpr int A_REGS = GB / 4;
   static_assert(S % 2 == 0 && S <= 8, "slice pairs; steps stay inside the padded width");
