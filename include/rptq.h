@@ -247,9 +247,9 @@ int32_t rptq_gemm_bf16(const void* x_hat, const void* w_hat, int64_t M, int32_t 
  *   Y[t,o] = sW_o * ( sum_i sX_i P_i[t,o] - colterm[o] - zW_o * rowterm[t] )
  * which equals sum_i sX_i sW_o Yq_i with
  *   Yq_i = P_i - zX_i wsum[o,i] - zW_o xsum[t,i] + n_i zX_i zW_o.
- * Products of few output tiles (at most 1440 tiles of 32 x 32, 8 clusters or more) split K among the waves of
- * a workgroup; of the others, rows up to 32 take the weight-streaming kernel, larger M the LDS-tiled one.  Every
- * result is deterministic; between kernels (other M or N) fp32 results differ by summation order.
+ * Products of few output tiles split K among the waves of a workgroup; of the others, rows up to 32 take the
+ * weight-streaming kernel, larger M the LDS-tiled one.  All of them add the clusters in the same order with the same
+ * roundings: the outputs of a token do not depend on the M or N of the call.
  *
  *  codes_packed device, M rows, `bits` in {3,4,8};  Wq_packed device (N, K_p)
  *  cluster_off,sX host [g+1],[g];  sW,colterm device fp32 [N]; zW device int32 [N]
@@ -267,8 +267,7 @@ int32_t rptq_cluster_gemm(const void* codes_packed, int64_t M, int32_t bits,
  * layer's rows were reordered offline into the next site's padded cluster order (perm_out
  * of rptq_fold_reorder = that site's perm_pad, N = its K_p), so the product leaves the
  * matrix cores already in that order and is quantized in place of being stored:
- *     h = bf16(Y[t,n])  (the value rptq_cluster_gemm's streaming or tiled kernel would have stored; round to nearest
- *                       even; where that call splits K its fp32 value can differ in the last place)
+ *     h = bf16(Y[t,n])  (the value rptq_cluster_gemm would have stored; round to nearest even)
  *     q = clamp(round(max(h,0) * inv_s_i) + z_i, ...)   i = next site's cluster of position n
  * exactly as rptq_ln_quant without LayerNorm does on a stored bf16 Y; pad positions get
  * code 0.  The bf16 tensor between the two layers is never written or read.

@@ -11,6 +11,14 @@ constexpr int kMaxWaves = 16;   // 1024 threads
 __device__ __forceinline__ float bf16_lo(uint32_t w) { return __uint_as_float(w << 16); }
 __device__ __forceinline__ float bf16_hi(uint32_t w) { return __uint_as_float(w & 0xffff0000u); }
 
+// Orders one wave's LDS accesses: what its lanes wrote before is read after.  (LDS executes a wave's instructions in
+// order, so no instruction is needed; the fences keep the compiler from moving an access across.)
+__device__ __forceinline__ void wave_lds_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
+}
+
 // ---- cross-lane sums on the DPP path (no LDS round trips) -------------------------------------
 template <int CTRL, int ROW_MASK>
 __device__ __forceinline__ double dpp_add(double v) {

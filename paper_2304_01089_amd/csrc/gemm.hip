@@ -807,7 +807,11 @@ int32_t launch_gemm(const void* codes, int64_t M, int32_t bits, const void* Wq, 
     qo = *quant_out;
     out_mode = qo.row_bytes * 8 / N;                        // bits of the codes written
   }
-  if (cw == nullptr && small_gemm_serves(M, N, geom.g, out_mode)) return launch_small_gemm(a, tab, bits, out_mode, st);
+  if (cw == nullptr) {
+    bool served = false;
+    if (int32_t s = launch_small_gemm(a, tab, bits, out_mode, st, &served)) return s;
+    if (served) return RPTQ_OK;
+  }
   if (bits == 3) return launch_bits<3>(a, tab, out_mode, qo, q_rowterm, st);
   if (bits == 4) return launch_bits<4>(a, tab, out_mode, qo, q_rowterm, st);
   return launch_bits<8>(a, tab, out_mode, qo, q_rowterm, st);

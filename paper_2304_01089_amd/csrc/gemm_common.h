@@ -76,70 +76,12 @@ struct ActFmt {
   static constexpr int kShift = (BITS == 8) ? 0 : (BITS == 4 ? 4 : 5);
 };
 
-#if defined(__HIPCC__)
-// 16 bytes of 4-bit codes (32 codes) -> 32 int8 values (code << 4), natural order.
-__device__ __forceinline__ void unpack4(const uint4 p, uint4* lo, uint4* hi) {
-  lo->x = p.x & 0xf0f0f0f0u;
-  lo->y = (p.x << 4) & 0xf0f0f0f0u;
-  lo->z = p.y & 0xf0f0f0f0u;
-  lo->w = (p.y << 4) & 0xf0f0f0f0u;
-  hi->x = p.z & 0xf0f0f0f0u;
-  hi->y = (p.z << 4) & 0xf0f0f0f0u;
-  hi->z = p.w & 0xf0f0f0f0u;
-  hi->w = (p.w << 4) & 0xf0f0f0f0u;
-}
-
-// 12 bytes of 3-bit codes (32 codes) -> 32 int8 values (code << 5), natural order.
-__device__ __forceinline__ void unpack3(uint32_t x0, uint32_t x1, uint32_t x2, uint4* lo, uint4* hi) {
-  lo->x = x0 & 0xe0e0e0e0u;
-  lo->y = (x0 << 3) & 0xe0e0e0e0u;
-  lo->z = x1 & 0xe0e0e0e0u;
-  lo->w = (x1 << 3) & 0xe0e0e0e0u;
-  hi->x = x2 & 0xe0e0e0e0u;
-  hi->y = (x2 << 3) & 0xe0e0e0e0u;
-  hi->z = ((x0 << 6) & 0xc0c0c0c0u) | ((x2 << 5) & 0x20202020u);
-  hi->w = ((x1 << 6) & 0xc0c0c0c0u) | ((x2 << 4) & 0x20202020u);
-}
-
 // OUT: what the output stage writes - kOutBf16 / kOutF32: Y; 3, 4 or 8: the next site's packed
 // codes of that many bits (ReLU optional) and the partial row sums its product needs.
 constexpr int kOutBf16 = 0, kOutF32 = 1;
 
-// Stores the outputs of one row and 16 bytes of columns (4 fp32 or 8 bf16, rounded to nearest even).
-template <bool YF32>
-__device__ __forceinline__ void store_outputs(const GemmArgs& a, const float* v, int64_t t, int n, bool vec_ok) {
-  typedef float f2 __attribute__((ext_vector_type(2)));
-  typedef __bf16 b2 __attribute__((ext_vector_type(2)));
-  unsigned char* ybase = static_cast<unsigned char*>(a.y);
-  if (YF32) {
-    if (vec_ok) {
-      *reinterpret_cast<float4*>(ybase + (t * a.N + n) * 4) = make_float4(v[0], v[1], v[2], v[3]);
-    } else {
-#pragma unroll
-      for (int e = 0; e < 4; ++e)
-        if (n + e < a.N) reinterpret_cast<float*>(ybase)[t * a.N + n + e] = v[e];
-    }
-  } else {
-    uint32_t w[4];
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const f2 pr = {v[(2 * e) % (YF32 ? 4 : 8)], v[(2 * e + 1) % (YF32 ? 4 : 8)]};
-      const b2 cv = __builtin_convertvector(pr, b2);
-      w[e] = *reinterpret_cast<const uint32_t*>(&cv);
-    }
-    if (vec_ok) {
-      *reinterpret_cast<uint4*>(ybase + (t * a.N + n) * 2) = make_uint4(w[0], w[1], w[2], w[3]);
-    } else {
-#pragma unroll
-      for (int e = 0; e < 8; ++e)
-        if (n + e < a.N) reinterpret_cast<uint16_t*>(ybase)[t * a.N + n + e] = static_cast<uint16_t>(w[e / 2] >> (16 * (e & 1)));
-    }
-  }
-}
-#endif
-
-// gemm_small.hip: the product with K split over a workgroup's waves, for few output tiles (the choice is made there)
-bool small_gemm_serves(int64_t M, int32_t N, int32_t g, int out_mode);
-int32_t launch_small_gemm(const GemmArgs& a, const GemmTab& tab, int bits, int out_mode, hipStream_t st);
+// gemm_small.hip: the product with K split over a workgroup's waves, for few output tiles.  *served tells whether it
+// took the call (the choice is made there).
+int32_t launch_small_gemm(const GemmArgs& a, const GemmTab& tab, int bits, int out_mode, hipStream_t st, bool* served);
 
 }  // namespace rptq

@@ -3,12 +3,18 @@
 //
 // The prefill kernel gives a workgroup a 64 x 256 tile and all of K; with 40 to 250 such tiles most of the
 // chip is idle and the few waves at work cannot keep enough bytes in flight.  Here the waves of a workgroup
-// share one small tile and split K among them: each runs its own pipeline over its range of K steps - its own
-// LDS stage, so there is no barrier in the loop - and the fp32 tiles are added in a fixed order at the end.
-// A cluster that two waves share is scaled in both (its integer sums are exact, so is their split).
-// Operand formats, MFMA use and rescale are those of the prefill kernel.
+// share one 32 x 32 tile and split K among them, each with its own pipeline and LDS stage.
+//
+// The result is the prefill kernel's, bit for bit: a token's outputs do not depend on how many rows or columns share
+// its call.  What the waves hand over is therefore integers: where a cluster, or a wave's share of K, ends, the wave
+// leaves its int32 tile in LDS (a piece).  The fp32 chain over the clusters - add a cluster's pieces (exact), convert,
+// times sX_i, add, in cluster order - is run by the workgroup's threads, each on its own outputs.  A piece is 4 KiB (2 KiB
+// up to 16 tokens), so K is walked in periods of as many clusters as LDS holds pieces of: the period's K steps are shared
+// out, a barrier, its pieces enter the chain, a barrier.
+// Operand formats, MFMA use and output arithmetic are those of the prefill kernel.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <type_traits>
 
 #include "device_common.h"
@@ -17,31 +23,62 @@
 
 namespace rptq {
 
+// 16 bytes of 4-bit codes (32 codes) -> 32 int8 values (code << 4), natural order.
+__device__ __forceinline__ void unpack4(const uint4 p, uint4* lo, uint4* hi) {
+  lo->x = p.x & 0xf0f0f0f0u;
+  lo->y = (p.x << 4) & 0xf0f0f0f0u;
+  lo->z = p.y & 0xf0f0f0f0u;
+  lo->w = (p.y << 4) & 0xf0f0f0f0u;
+  hi->x = p.z & 0xf0f0f0f0u;
+  hi->y = (p.z << 4) & 0xf0f0f0f0u;
+  hi->z = p.w & 0xf0f0f0f0u;
+  hi->w = (p.w << 4) & 0xf0f0f0f0u;
+}
+
+// 12 bytes of 3-bit codes (32 codes) -> 32 int8 values (code << 5), natural order.
+__device__ __forceinline__ void unpack3(uint32_t x0, uint32_t x1, uint32_t x2, uint4* lo, uint4* hi) {
+  lo->x = x0 & 0xe0e0e0e0u;
+  lo->y = (x0 << 3) & 0xe0e0e0e0u;
+  lo->z = x1 & 0xe0e0e0e0u;
+  lo->w = (x1 << 3) & 0xe0e0e0e0u;
+  hi->x = x2 & 0xe0e0e0e0u;
+  hi->y = (x2 << 3) & 0xe0e0e0e0u;
+  hi->z = ((x0 << 6) & 0xc0c0c0c0u) | ((x2 << 5) & 0x20202020u);
+  hi->w = ((x1 << 6) & 0xc0c0c0c0u) | ((x2 << 4) & 0x20202020u);
+}
+
+constexpr int kSmallTile = 32;             // output rows and columns of a workgroup
+constexpr int kSmallSlices = 4;            // slices (of 32 codes) per K step
 constexpr int kSmallPad = 32;              // bytes added to a slice's LDS stride: the staging stores of 8 consecutive lanes
                                            // (two rows x four slices) fall into distinct 16-byte bank groups
+constexpr int kSmallSlicePitch = 2 * kSmallTile * 16 + kSmallPad;    // [half][row][16 B]
+constexpr int kSmallStage = kSmallSlices * kSmallSlicePitch;         // one wave's activations of a K step
+constexpr int kMaxPeriods = 16;
+constexpr int kMaxPieces = 60;             // of one period (a lane each)
 
-// Waves: WGN side by side over the columns x KS over K; a wave's tile is 32 WM tokens x 32 WN channels; a K step
-// has S slices of 32 codes.
-//
-// The loop body is one step, with one register set of weights and one of activations, each refilled with the
-// next step's bytes as it is used up, and one LDS stage: a wave that has little to do runs every instruction a
-// few times only, so the code's own way through the instruction cache counts.  (The rescale of a finished cluster exists
-// once per slice.  Four steps per pass with as many register sets of weights in flight and two LDS stages took 34.8 us
-// where this takes 30.3, at 512 x 8192 x 2048, and 17.9 against 15.4 at 32 x 20480 x 5120.)
-// Latency is covered by several waves per SIMD instead.  (The second launch bound keeps the accumulators out of the
-// AGPRs, where a rescale costs a move per element.)
-template <int BITS, int WM, int WN, int WGN, int KS, int S, int OUT>
-__global__ void __launch_bounds__(WGN * KS * 64, WM * WN == 1 ? 4 : 2) small_gemm_kernel(GemmArgs a, GemmTab tab) {
+// How the workgroups walk K (by value).
+struct SmallPlan {
+  int32_t periods;
+  int32_t end[kMaxPeriods];                // first K step after period p
+};
+
+// The loop body is one step, with one register set of weights and one of activations, each refilled with the next
+// step's bytes as it is used up, and one LDS stage: a wave that has little to do runs every instruction a few times
+// only, so the code's own way through the instruction cache counts.  Latency is covered by several waves per SIMD.
+// (The second launch bound keeps the accumulators out of the AGPRs, where reading one costs a move.)
+template <int BITS, int KS, int ROWS, int OUT>
+__global__ void __launch_bounds__(KS * 64, 4) small_gemm_kernel(GemmArgs a, GemmTab tab, SmallPlan plan) {
   constexpr bool YF32 = OUT == kOutF32;
-  constexpr int NT = WGN * KS * 64;
-  constexpr int BM = WM * 32;
-  constexpr int BN = WGN * WN * 32;
-  constexpr int A_SLICE = 2 * BM * 16 + kSmallPad;       // [half][row][16 B]
-  constexpr int A_STAGE = S * A_SLICE;
+  constexpr int NT = KS * 64;
+  constexpr int S = kSmallSlices, BM = kSmallTile, BN = kSmallTile;
+  constexpr int A_SLICE = kSmallSlicePitch;
   constexpr int A_PER = BM * S / 64;                     // (row, slice) units per lane and K step
   constexpr int GB = ActFmt<BITS>::kGroupBytes;
   constexpr int A_REGS = GB / 4;
+  constexpr int PIECE = ROWS * BN * 4;                   // bytes; ROWS: tokens that a piece holds (M or more, or 32)
+  constexpr int E = BM * BN / NT;                        // outputs of a thread in the chain over the clusters
   static_assert(S % 2 == 0 && S <= 8, "slice pairs; steps stay inside the padded width");
+  static_assert(E == 2 || E == 4, "a thread's outputs lie in one register quad");
   typedef unsigned u4v __attribute__((ext_vector_type(4)));
   typedef unsigned u3v __attribute__((ext_vector_type(3)));
   constexpr int kRsrcFlags = 0x00020000;
@@ -49,9 +86,9 @@ __global__ void __launch_bounds__(WGN * KS * 64, WM * WN == 1 ? 4 : 2) small_gem
   extern __shared__ __align__(16) unsigned char smem[];
   const int tid = threadIdx.x;
   const int lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int wn = wave % WGN, kg = wave / WGN;
-  unsigned char* sA = smem + wave * A_STAGE;              // this wave's stage
+  const int kg = __builtin_amdgcn_readfirstlane(tid >> 6);
+  unsigned char* sA = smem + kg * kSmallStage;            // this wave's stage
+  unsigned char* pieces = smem + KS * kSmallStage;        // [piece][register quad][half][token][16 B]
 
   // every XCD gets a contiguous range of tiles, the row tiles of one column tile back to back
   const int total = a.tiles_m * a.tiles_n;
@@ -61,19 +98,13 @@ __global__ void __launch_bounds__(WGN * KS * 64, WM * WN == 1 ? 4 : 2) small_gem
   const int64_t m0 = static_cast<int64_t>(tm) * BM;
   const int n0 = tn * BN;
 
-  // ---- this wave's K steps ------------------------------------------------------------------
-  const int all_steps = (a.used_slices + S - 1) / S;
-  const int step0 = all_steps * kg / KS;
-  const int steps = all_steps * (kg + 1) / KS - step0;
-  const int last = (steps > 0 ? steps : 1) - 1;           // (an empty range loads a valid step and uses nothing)
-
   const int64_t rows_here = (a.M - m0) < BM ? (a.M - m0) : BM;
   const int wblocks = a.slices / (kWBlockCols / kGroup);   // packed weight blocks per 32-row band
   const __amdgpu_buffer_rsrc_t a_rsrc = __builtin_amdgcn_make_buffer_rsrc(
       const_cast<uint8_t*>(a.codes) + m0 * a.row_bytes, 0, static_cast<int>(rows_here) * a.row_bytes, kRsrcFlags);
   const __amdgpu_buffer_rsrc_t w_rsrc = __builtin_amdgcn_make_buffer_rsrc(
-      const_cast<uint8_t*>(a.Wq) + static_cast<size_t>(n0 / 32) * wblocks * 2048, 0, (BN / 32) * wblocks * 2048, kRsrcFlags);
-  int a_off[A_PER], a_lds[A_PER], w_off[WN];
+      const_cast<uint8_t*>(a.Wq) + static_cast<size_t>(tn) * wblocks * 2048, 0, wblocks * 2048, kRsrcFlags);
+  int a_off[A_PER], a_lds[A_PER];
 #pragma unroll
   for (int i = 0; i < A_PER; ++i) {
     const int unit = lane + i * 64;
@@ -82,14 +113,43 @@ __global__ void __launch_bounds__(WGN * KS * 64, WM * WN == 1 ? 4 : 2) small_gem
     a_off[i] = lrow * a.row_bytes + s * GB;
     a_lds[i] = s * A_SLICE + row * 16;
   }
+
+  // ---- this thread's E outputs: tokens vary fastest, then register quads (four columns) ----------
+  typedef float fE __attribute__((ext_vector_type(E)));
+  constexpr int kOutThreads = PIECE / (4 * E);
+  const int my_out = tid % kOutThreads;                     // (surplus threads go along and store nothing)
+  const int o_tok = my_out * E / 4 % ROWS, o_n = n0 + my_out * E / 4 / ROWS * 4 + my_out * E % 4;
+  float p_sw[E], p_ct[E], p_zw[E];
+  const float p_rt = a.rowterm[m0 + (o_tok < rows_here ? o_tok : 0)];
 #pragma unroll
-  for (int j = 0; j < WN; ++j) w_off[j] = (wn * WN + j) * wblocks * 2048 + lane * 16;
+  for (int e = 0; e < E; ++e) {                             // (requested here: used at the very end)
+    const int ne = min(o_n + e, a.N - 1);
+    p_sw[e] = a.sW[ne];
+    p_ct[e] = a.colterm[ne];
+    p_zw[e] = static_cast<float>(a.zW[ne]);
+  }
+
+  // ---- this wave's K steps: its share of every period ----------------------------------------
+  const int all_steps = (a.used_slices + S - 1) / S;
+  const int tab_period = plan.end[lane % kMaxPeriods];      // lane p: end of period p
+  struct Cursor { int p, t, e; };                           // period, step, end of the wave's share of that period
+  auto period_begin = [&](int p) { return p ? __builtin_amdgcn_readlane(tab_period, p - 1) : 0; };
+  // where wave w's share of n steps from b begins (of fewer steps than waves, the first waves get one each)
+  auto share_begin = [&](int b, int n, int w) { return b + (n < KS ? min(w, n) : static_cast<int>(static_cast<unsigned>(n * w) / KS)); };
+  auto settle = [&](Cursor& c) {                            // on to the next period that has a step for this wave
+    while (c.t >= c.e && c.p + 1 < plan.periods) {
+      ++c.p;
+      const int b = period_begin(c.p), n = __builtin_amdgcn_readlane(tab_period, c.p) - b;
+      c.t = share_begin(b, n, kg);
+      c.e = share_begin(b, n, kg + 1);
+    }
+  };
 
   uint32_t ra[A_PER][A_REGS];
-  u4v wreg[WN][S / 2];
-  auto clamp_step = [&](int t) { return step0 + (t < last ? t : last); };
-  auto load_a = [&](int t) {
-    const int soff = clamp_step(t) * (S * GB);
+  u4v wreg[S / 2];
+  // (behind a wave's last step a valid step is loaded again and never used)
+  auto load_a = [&](const Cursor& c) {
+    const int soff = min(c.t, all_steps - 1) * (S * GB);
 #pragma unroll
     for (int i = 0; i < A_PER; ++i) {
       if (A_REGS == 3) {
@@ -106,9 +166,8 @@ __global__ void __launch_bounds__(WGN * KS * 64, WM * WN == 1 ? 4 : 2) small_gem
       }
     }
   };
-  auto load_w_pair = [&](int t, int j, int p) {             // two slices of column block j
-    const int pair = clamp_step(t) * (S / 2) + p;            // (a packed block holds two pairs, 1 KiB each)
-    wreg[j][p] = __builtin_amdgcn_raw_buffer_load_b128(w_rsrc, w_off[j], pair * 1024, 0);
+  auto load_w_pair = [&](const Cursor& c, int p) {          // two slices (a packed block holds two pairs, 1 KiB each)
+    wreg[p] = __builtin_amdgcn_raw_buffer_load_b128(w_rsrc, lane * 16, (min(c.t, all_steps - 1) * (S / 2) + p) * 1024, 0);
   };
   auto store_a = [&](int i) {                               // unpack a unit to int8 into LDS
     unsigned char* d = sA + a_lds[i];
@@ -125,223 +184,262 @@ __global__ void __launch_bounds__(WGN * KS * 64, WM * WN == 1 ? 4 : 2) small_gem
     *reinterpret_cast<uint4*>(d + BM * 16) = hi;
   };
 
-  v16i acc[WM][WN];
-  v16f facc[WM][WN];
-  auto clear_tile = [&](int i, int j) {                     // (opaque zeros: see the prefill kernel)
+  v16i acc;                                                 // 2^shift * this wave's part of P_i
+  auto clear_acc = [&]() {                                  // (opaque zeros: see the prefill kernel)
 #pragma unroll
     for (int r = 0; r < 16; r += 2) {
       unsigned long long zz;
       asm volatile("v_mov_b64 %0, 0" : "=v"(zz));
-      acc[i][j][r] = static_cast<int>(zz);
-      acc[i][j][r + 1] = static_cast<int>(zz >> 32);
+      acc[r] = static_cast<int>(zz);
+      acc[r + 1] = static_cast<int>(zz >> 32);
     }
   };
-#pragma unroll
-  for (int i = 0; i < WM; ++i)
-#pragma unroll
-    for (int j = 0; j < WN; ++j) {
-      clear_tile(i, j);
-#pragma unroll
-      for (int r = 0; r < 16; ++r) facc[i][j][r] = 0.0f;
-    }
+  clear_acc();
 
-  // cluster tables in one register each (lane i: cluster i); this wave starts inside cluster ci
+  // cluster tables in one register each (lane i: cluster i)
   const float tab_scale = tab.scale[lane];
   const int tab_end = tab.slice_end[lane];
-  int ci = __builtin_popcountll(__ballot(lane < tab.g && tab_end <= step0 * S));
-  int next_end = __builtin_amdgcn_readlane(tab_end, ci & 63);
-  auto rescale = [&]() {
-    const float sc = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, tab_scale), ci & 63));
+  auto finished_before = [&](int slice) { return __builtin_popcountll(__ballot(lane < tab.g && tab_end <= slice)); };
+  // Leaves this wave's part of a cluster in a piece.  A wave leaves one where a cluster ends and one where its share ends
+  // (empty if a cluster ends there too), so that pieces numbered cluster (from the period's first) plus wave
+  // follow each other along K without a gap.
+  const bool tok_ok = (lane & 31) < ROWS;
+  unsigned char* my_quads = pieces + (lane >> 5) * (ROWS * 16) + (lane & 31) * 16;
+  auto leave = [&](int piece) {
+    if (tok_ok) {
 #pragma unroll
-    for (int i = 0; i < WM; ++i)
+      for (int q = 0; q < 4; ++q)
+        *reinterpret_cast<int4*>(my_quads + piece * PIECE + q * (ROWS * 32)) =
+            make_int4(acc[q * 4], acc[q * 4 + 1], acc[q * 4 + 2], acc[q * 4 + 3]);
+    }
+    clear_acc();
+  };
+
+  // ---- the chain over the clusters: E neighbouring outputs per thread ---------------------------
+  typedef int iE __attribute__((ext_vector_type(E)));
+  const iE* my_ints = reinterpret_cast<const iE*>(pieces) + my_out;
+  float f[E];
+  int v[E];                                                 // the integers of the cluster under way
 #pragma unroll
-      for (int j = 0; j < WN; ++j) {
+  for (int e = 0; e < E; ++e) {
+    f[e] = 0.0f;
+    v[e] = 0;
+  }
+  // `end_scale`, lane j: sX of the cluster that piece j ends, else 0 (f + v * 0 is f: f is never -0); `go_on`, lane j:
+  // all ones where the cluster goes on in piece j + 1
+  auto chain = [&](int count, int end_scale, int go_on) {
+    int j = 0;
+    auto some = [&](auto together) {
+      constexpr int U = decltype(together)::value;
+      iE x[U];
 #pragma unroll
-        for (int r = 0; r < 16; ++r) facc[i][j][r] = fmaf(static_cast<float>(acc[i][j][r]), sc, facc[i][j][r]);
-        clear_tile(i, j);
+      for (int u = 0; u < U; ++u) x[u] = my_ints[(j + u) * kOutThreads];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const float sc = __builtin_bit_cast(float, __builtin_amdgcn_readlane(end_scale, j + u));
+        const int keep = __builtin_amdgcn_readlane(go_on, j + u);
+#pragma unroll
+        for (int e = 0; e < E; ++e) {
+          v[e] += x[u][e];
+          f[e] = fmaf(static_cast<float>(v[e]), sc, f[e]);
+          v[e] &= keep;
+        }
       }
+      j += U;
+    };
+    while (j + 4 <= count) some(std::integral_constant<int, 4>());
+    while (j < count) some(std::integral_constant<int, 1>());
   };
 
   // ---- main loop --------------------------------------------------------------------------------
-  load_a(0);
+  Cursor nxt = {-1, 0, 0};                                  // the step whose operands are requested next
+  settle(nxt);
+  load_a(nxt);
 #pragma unroll
-  for (int p = 0; p < S / 2; ++p)
-#pragma unroll
-    for (int j = 0; j < WN; ++j) load_w_pair(0, j, p);
+  for (int p = 0; p < S / 2; ++p) load_w_pair(nxt, p);
 #pragma unroll
   for (int i = 0; i < A_PER; ++i) store_a(i);
-  load_a(1);
-  __builtin_amdgcn_wave_barrier();                          // (one wave: LDS executes its instructions in order)
+  ++nxt.t;
+  settle(nxt);
+  load_a(nxt);
+  wave_lds_fence();
 
   const int a_frag = (lane >> 5) * (BM * 16) + (lane & 31) * 16;
-  v4i fa[2][WM], fb[2][WN];
-  auto load_frags = [&](int s) {
-#pragma unroll
-    for (int i = 0; i < WM; ++i) fa[s & 1][i] = *reinterpret_cast<const v4i*>(sA + s * A_SLICE + a_frag + i * 512);
-  };
+  v4i fa[2], fb[2];
+  auto load_frags = [&](int s) { fa[s & 1] = *reinterpret_cast<const v4i*>(sA + s * A_SLICE + a_frag); };
   auto unpack_w = [&](int s) {
-#pragma unroll
-    for (int j = 0; j < WN; ++j) {
-      const u4v w = wreg[j][s >> 1];
-      const uint32_t x = (s & 1) ? w.z : w.x, y = (s & 1) ? w.w : w.y;
-      fb[s & 1][j][0] = static_cast<int>(x & 0xf0f0f0f0u);
-      fb[s & 1][j][1] = static_cast<int>((x << 4) & 0xf0f0f0f0u);
-      fb[s & 1][j][2] = static_cast<int>(y & 0xf0f0f0f0u);
-      fb[s & 1][j][3] = static_cast<int>((y << 4) & 0xf0f0f0f0u);
-    }
+    const u4v w = wreg[s >> 1];
+    const uint32_t x = (s & 1) ? w.z : w.x, y = (s & 1) ? w.w : w.y;
+    fb[s & 1][0] = static_cast<int>(x & 0xf0f0f0f0u);
+    fb[s & 1][1] = static_cast<int>((x << 4) & 0xf0f0f0f0u);
+    fb[s & 1][2] = static_cast<int>(y & 0xf0f0f0f0u);
+    fb[s & 1][3] = static_cast<int>((y << 4) & 0xf0f0f0f0u);
   };
   load_frags(0);
   unpack_w(0);
-  for (int t = 0; t < steps; ++t) {
+  for (int p = 0; p < plan.periods; ++p) {
+    const int b = period_begin(p), end = __builtin_amdgcn_readlane(tab_period, p);
+    const Cursor mine = {p, share_begin(b, end - b, kg), share_begin(b, end - b, kg + 1)};
+    const int first = finished_before(b * S);
+    int ci = finished_before(mine.t * S);                   // the cluster this share starts in
+    int next_end = __builtin_amdgcn_readlane(tab_end, ci & 63);
+    for (int t = mine.t; t < mine.e; ++t) {
 #pragma unroll
-    for (int s = 0; s < S; ++s) {
-      if (s + 1 < S) {                                      // next slice's operands
-        load_frags(s + 1);
-        unpack_w(s + 1);
-      } else {                                              // every read of this step is issued: the stage takes the next step
-        __builtin_amdgcn_wave_barrier();
+      for (int s = 0; s < S; ++s) {
+        if (s + 1 < S) {                                    // next slice's operands
+          load_frags(s + 1);
+          unpack_w(s + 1);
+        } else {                                            // every read of this step is issued: the stage takes the next step
+          wave_lds_fence();
 #pragma unroll
-        for (int i = 0; i < A_PER; ++i) store_a(i);
-        load_a(t + 2);
-        __builtin_amdgcn_wave_barrier();
-        load_frags(0);
-        unpack_w(0);                                        // (pair 0 already holds the next step)
-      }
-      if ((s & 1) == 0) {                                   // both slices of pair s/2 are expanded
-#pragma unroll
-        for (int j = 0; j < WN; ++j) load_w_pair(t + 1, j, s >> 1);
-      }
-#pragma unroll
-      for (int i = 0; i < WM; ++i)
-#pragma unroll
-        for (int j = 0; j < WN; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(fb[s & 1][j], fa[s & 1][i], acc[i][j], 0, 0, 0);
-      if ((step0 + t) * S + s + 1 == next_end) {            // cluster ci is complete (uniform branch)
-        rescale();
-        ++ci;
-        next_end = __builtin_amdgcn_readlane(tab_end, ci & 63);
+          for (int i = 0; i < A_PER; ++i) store_a(i);
+          ++nxt.t;
+          settle(nxt);
+          load_a(nxt);
+          wave_lds_fence();
+          load_frags(0);
+          unpack_w(0);                                      // (pair 0 already holds the next step)
+        }
+        if ((s & 1) == 0) load_w_pair(nxt, s >> 1);          // both slices of pair s/2 are expanded
+        acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(fb[s & 1], fa[s & 1], acc, 0, 0, 0);
+        if (t * S + s + 1 == next_end) {                    // cluster ci ends here (uniform branch)
+          leave(ci - first + kg);
+          ++ci;
+          next_end = __builtin_amdgcn_readlane(tab_end, ci & 63);
+        }
       }
     }
+    if (mine.t < mine.e && ci < tab.g) leave(ci - first + kg);
+    __syncthreads();
+    const bool last = p + 1 == plan.periods;
+    const int until = finished_before(end * S);             // clusters first .. until - 1 end in this period
+    int piece = lane - first;                               // lane i: the piece in which cluster i ends
+#pragma unroll
+    for (int w = 1; w < KS; ++w) piece += share_begin(b, end - b, w) * S < tab_end ? 1 : 0;
+    const int to = (lane >= first && lane < until ? piece : 63) * 4;
+    const int end_scale = __builtin_amdgcn_ds_permute(to, __builtin_bit_cast(int, tab_scale));
+    const int go_on = __builtin_amdgcn_ds_permute(to, 1) - 1;
+    // (the last wave of the last period leaves no piece behind the last cluster)
+    chain(until - first + min(end - b, KS) - (last ? 1 : 0), end_scale, go_on);
+    if (!last) __syncthreads();                             // the pieces have been read
   }
-  rescale();                                                // the part of a cluster that another wave goes on with (else zeros)
 
-  // ---- sum over the K ranges, zero-point terms, output scale, store -------------------------------
-  // Every wave leaves its fp32 tile in LDS, row-major; a thread then owns a group of columns, adds the K ranges' values in
-  // order in fp64 and finishes the prefill kernel's arithmetic there, with one rounding to fp32 at the end (norm of the
-  // error against float64 on seven shapes: 4.6e-8 to 6.4e-8; unsplit 5.8e-8 to 9.0e-8; with these sums in fp32 5.9e-8 to
-  // 8.8e-8).
-  constexpr int TP = BN + 4;
-  float* tile = reinterpret_cast<float*>(smem);             // [KS][BM][TP]
-  __syncthreads();                                          // every wave is done with its stage
+  // ---- zero-point terms, output scale, store: the prefill kernel's arithmetic ------------------------
+  const int64_t t = m0 + o_tok;
+  if (tid >= kOutThreads || t >= a.M) return;
+  float y[E];
 #pragma unroll
-  for (int i = 0; i < WM; ++i)
+  for (int e = 0; e < E; ++e) y[e] = p_sw[e] * ((f[e] - p_ct[e]) - p_zw[e] * p_rt);
+  const bool vec_ok = (a.N % E) == 0 && o_n < a.N;
+  if (YF32) {
+    float* dst = static_cast<float*>(a.y) + t * a.N + o_n;
+    if (vec_ok) {
+      fE o;
 #pragma unroll
-    for (int j = 0; j < WN; ++j)
+      for (int e = 0; e < E; ++e) o[e] = y[e];
+      *reinterpret_cast<fE*>(dst) = o;
+    } else {
 #pragma unroll
-      for (int q = 0; q < 4; ++q)
-        *reinterpret_cast<float4*>(tile + (kg * BM + i * 32 + (lane & 31)) * TP + (wn * WN + j) * 32 + q * 8 + (lane >> 5) * 4) =
-            make_float4(facc[i][j][q * 4], facc[i][j][q * 4 + 1], facc[i][j][q * 4 + 2], facc[i][j][q * 4 + 3]);
-  __syncthreads();
-  constexpr int CW = YF32 ? 4 : 8;                          // outputs per 16-byte store
-  constexpr int CPR = BN / CW;
-  static_assert(NT % CPR == 0, "a thread keeps its columns");
-  const int cc = tid % CPR;
-  const int n = n0 + cc * CW;
-  float sw[CW], ct[CW];
-  int zw[CW];
+      for (int e = 0; e < E; ++e)
+        if (o_n + e < a.N) dst[e] = y[e];
+    }
+  } else {
+    typedef __bf16 bE __attribute__((ext_vector_type(E)));
+    fE o;
 #pragma unroll
-  for (int e = 0; e < CW; ++e) {
-    const int ne = n + e < a.N ? n + e : a.N - 1;           // (columns past N are never stored)
-    sw[e] = a.sW[ne];
-    ct[e] = a.colterm[ne];
-    zw[e] = a.zW[ne];
-  }
-  const bool vec_ok = (a.N % 8) == 0 && n + CW <= a.N;
-  for (int row = tid / CPR; row < BM; row += NT / CPR) {
-    const int64_t t = m0 + row;
-    if (t >= a.M || n >= a.N) continue;
-    const double rt = a.rowterm[t];
-    double sum[CW];
+    for (int e = 0; e < E; ++e) o[e] = y[e];
+    const bE h = __builtin_convertvector(o, bE);            // round to nearest even
+    __bf16* dst = static_cast<__bf16*>(a.y) + t * a.N + o_n;
+    if (vec_ok) {
+      *reinterpret_cast<bE*>(dst) = h;
+    } else {
 #pragma unroll
-    for (int e = 0; e < CW; ++e) sum[e] = 0.0;
-#pragma unroll
-    for (int k = 0; k < KS; ++k)
-#pragma unroll
-      for (int e4 = 0; e4 < CW / 4; ++e4) {
-        const float4 f = *reinterpret_cast<const float4*>(tile + (k * BM + row) * TP + cc * CW + e4 * 4);
-        sum[e4 * 4 + 0] += f.x;
-        sum[e4 * 4 + 1] += f.y;
-        sum[e4 * 4 + 2] += f.z;
-        sum[e4 * 4 + 3] += f.w;
-      }
-    float v[CW];
-#pragma unroll
-    for (int e = 0; e < CW; ++e)
-      v[e] = static_cast<float>(static_cast<double>(sw[e]) * ((sum[e] - ct[e]) - static_cast<double>(zw[e]) * rt));
-    store_outputs<YF32>(a, v, t, n, vec_ok);
+      for (int e = 0; e < E; ++e)
+        if (o_n + e < a.N) dst[e] = h[e];
+    }
   }
 }
 
-template <int BITS, int WM, int WN, int WGN, int KS, int S, int OUT>
-static int32_t launch_small_cfg(const GemmArgs& a, const GemmTab& tab, hipStream_t st) {
-  constexpr int BM = WM * 32, BN = WGN * WN * 32;
-  constexpr size_t stages = static_cast<size_t>(WGN) * KS * S * (2 * BM * 16 + kSmallPad);
-  constexpr size_t tiles = static_cast<size_t>(KS) * BM * (BN + 4) * 4;
-  constexpr size_t shmem = stages > tiles ? stages : tiles;
-  static_assert(shmem <= 160 * 1024, "LDS of a compute unit");
-  auto kern = small_gemm_kernel<BITS, WM, WN, WGN, KS, S, OUT>;
+// Divides K into periods (one if LDS holds all pieces).  A period that n clusters reach into leaves up to n + ks pieces;
+// it ends on a multiple of ks steps where it is long enough, so that the shares are equal.  False: too many periods.
+static bool make_small_plan(const GemmArgs& a, const GemmTab& tab, int ks, int piece_bytes, int lds_bytes, SmallPlan* plan,
+                            int* used) {
+  const int all_steps = (a.used_slices + kSmallSlices - 1) / kSmallSlices;
+  const int stages = ks * kSmallStage;
+  const int most = std::min((lds_bytes - stages) / piece_bytes, kMaxPieces) - ks;
+  if (most < kSmallSlices) return false;                    // (a step touches up to four clusters)
+  plan->periods = 0;
+  int b = 0, first = 0;                                      // first step of the period; the cluster it starts in
+  while (b < all_steps) {
+    if (plan->periods == kMaxPeriods) return false;
+    int e = all_steps;
+    if (tab.g - first > most) {
+      e = tab.slice_end[first + most - 1] / kSmallSlices;    // (the step that goes past it touches one more)
+      if (e - b > ks) e = b + (e - b) / ks * ks;
+    }
+    plan->end[plan->periods++] = b = e;
+    while (first < tab.g && tab.slice_end[first] <= b * kSmallSlices) ++first;
+  }
+  for (int p = plan->periods; p < kMaxPeriods; ++p) plan->end[p] = all_steps;
+  *used = stages + piece_bytes * (std::min(most, tab.g) + ks);
+  return true;
+}
+
+template <int BITS, int KS, int ROWS, int OUT>
+static int32_t launch_small_cfg(const GemmArgs& a, const GemmTab& tab, int lds_bytes, hipStream_t st, bool* served) {
+  SmallPlan plan;
+  int shmem = 0;
+  if (!make_small_plan(a, tab, KS, ROWS * kSmallTile * 4, lds_bytes, &plan, &shmem)) return RPTQ_OK;
+  auto kern = small_gemm_kernel<BITS, KS, ROWS, OUT>;
   static LdsGrant lds_granted;
-  if (int32_t s = ensure_dynamic_lds(reinterpret_cast<const void*>(kern), shmem, &lds_granted, st)) return s;
+  if (shmem > 64 * 1024) {
+    // (the limit is raised to the largest size at once; while a graph is recorded it cannot be, and the other kernels
+    // give the same result)
+    const int32_t s = ensure_dynamic_lds(reinterpret_cast<const void*>(kern), lds_bytes, &lds_granted, st);
+    if (s == RPTQ_ERR_CAPTURE) return RPTQ_OK;
+    if (s) return s;
+  }
   GemmArgs b = a;
-  b.tiles_n = (a.N + BN - 1) / BN;
-  b.tiles_m = static_cast<int32_t>((a.M + BM - 1) / BM);
+  b.tiles_n = (a.N + kSmallTile - 1) / kSmallTile;
+  b.tiles_m = static_cast<int32_t>((a.M + kSmallTile - 1) / kSmallTile);
   const dim3 grid(static_cast<unsigned>(b.tiles_n) * static_cast<unsigned>(b.tiles_m));
-  hipLaunchKernelGGL(kern, grid, dim3(WGN * KS * 64), shmem, st, b, tab);
+  *served = true;
+  hipLaunchKernelGGL(kern, grid, dim3(KS * 64), shmem, st, b, tab, plan);
   RPTQ_HIP(hipGetLastError());
   return RPTQ_OK;
 }
 
-// Which split serves a product, by its number of 32 x 32 output tiles (T).  Measured, us: the best tile of the prefill /
-// decode kernel first, then 32 x 32 with K in 8, in 4, 32 x 64 with K in 4:
-//     1 x  8192 x  2048 (T =  256):  8.6   5.8   6.1   8.4      128 x 3072 x  768 (T =  384):  9.7   5.8   5.1   6.6
-//    32 x  5120 x 12288 (T =  160): 28.8  12.1  15.4  19.9       32 x 20480 x 5120 (T =  640): 17.0  18.7  15.4  18.4
-//    64 x  2048 x  2048 (T =  128): 16.5   5.7   5.9   8.4       64 x 16000 x 5120 (T = 1000): 22.4        18.7
-//   200 x  5120 x  5120 (T = 1120): 22.6  25.7  21.8  21.4      333 x 4099 x 4072 (T = 1419): 23.5  29.0  24.5  21.2
-//   512 x  3000 x  2048 (T = 1504): 12.8              13.7      512 x 4096 x 5120 (T = 2048): 24.0              28.2
-//    16 x 49152 x 12288 (T = 1536): 55.8  74.5  72.6  61.2  (decode kernel: it streams the weights at the rate of memory)
-// A cluster that is split between waves is rounded once per part.  With at least as many clusters as K ranges the sums in
-// fp64 more than make up for that (figures above); with fewer, the parts can be larger than their sum: not split.
-constexpr int kSmallMinClusters = 8;
-enum SmallSplit { kSplitNone, kSplit32x32k8, kSplit32x32k4, kSplit32x64k4 };
-static SmallSplit small_split(int64_t M, int32_t N, int32_t g) {
-  if (g < kSmallMinClusters) return kSplitNone;
-  const int64_t tiles = (M + 31) / 32 * ((N + 31) / 32);
-  if (tiles <= 256) return kSplit32x32k8;
-  if (tiles <= 1024) return kSplit32x32k4;
-  if (tiles <= 1440 && M > 32) return kSplit32x64k4;
-  return kSplitNone;
-}
-
-bool small_gemm_serves(int64_t M, int32_t N, int32_t g, int out_mode) {
-  return (out_mode == kOutBf16 || out_mode == kOutF32) && small_split(M, N, g) != kSplitNone;
-}
-
+// Which calls are split, by the number of 32 x 32 output tiles (T).  us, unsplit | K in 8 | K in 4; g clusters:
+//                                g = 8                 g = 16                g = 32
+//     1 x  8192 x  2048 (T 256)   7.4 |  5.9 |  6.1     8.6 |  6.6 |  6.9    10.4 |  7.9 |  9.3
+//    32 x  5120 x  5120 (T 160)  12.8 |  7.5 |  8.2    14.2 |  8.3 |  9.4    16.0 | 10.5 | 12.8
+//    32 x  5120 x 20480 (T 160)  40.2 | 15.5 | 20.6    41.4 | 16.0 | 22.0    43.2 | 18.6 | 25.2
+//   256 x  1024 x  1024 (T 256)   7.2 |  5.8 |  5.5     9.1 |  6.4 |  6.7    12.1 |  8.8 | 10.1
+//    32 x 12288 x  2048 (T 384)   7.7 | 10.8 |  7.1     9.0 | 12.1 |  9.0    10.7 | 16.4 | 13.4
+//   128 x  3072 x   768 (T 384)   6.9 |  8.7 |  5.8     8.6 | 10.8 |  8.9    12.2 | 15.3 | 12.1
+//    64 x  5120 x  5120 (T 320)  16.4 | 13.4 |  9.7    18.3 | 15.2 | 11.4    21.2 | 19.6 | 16.1
+//    16 x 16384 x 12288 (T 512)  26.8 | 19.2 | 19.1    28.0 | 23.7 | 19.6    29.8 | 26.9 | 23.2
+// Eight ranges fill the chip with one workgroup per compute unit (T up to 256), four with two.  What a split costs is the
+// chain, by the cluster; beyond 256 tiles, where less is gained, it pays from four slices per cluster on average.
 template <int BITS, int OUT>
-static int32_t launch_small_out(const GemmArgs& a, const GemmTab& tab, hipStream_t st) {
-  switch (small_split(a.M, a.N, tab.g)) {
-    case kSplit32x32k8: return launch_small_cfg<BITS, 1, 1, 1, 8, 4, OUT>(a, tab, st);
-    case kSplit32x32k4: return launch_small_cfg<BITS, 1, 1, 1, 4, 4, OUT>(a, tab, st);
-    case kSplit32x64k4: return launch_small_cfg<BITS, 1, 2, 1, 4, 4, OUT>(a, tab, st);
-    case kSplitNone: break;
-  }
-  return RPTQ_ERR_SHAPE;
+static int32_t launch_small_out(const GemmArgs& a, const GemmTab& tab, hipStream_t st, bool* served) {
+  const int64_t tiles = (a.M + kSmallTile - 1) / kSmallTile * ((a.N + kSmallTile - 1) / kSmallTile);
+  if (tiles <= 256)
+    return a.M <= 16 ? launch_small_cfg<BITS, 8, 16, OUT>(a, tab, 160 * 1024, st, served)
+                     : launch_small_cfg<BITS, 8, 32, OUT>(a, tab, 160 * 1024, st, served);
+  if (tiles <= 512 && a.used_slices >= 4 * tab.g)
+    return a.M <= 16 ? launch_small_cfg<BITS, 4, 16, OUT>(a, tab, 80 * 1024, st, served)
+                     : launch_small_cfg<BITS, 4, 32, OUT>(a, tab, 80 * 1024, st, served);
+  return RPTQ_OK;
 }
 
-int32_t launch_small_gemm(const GemmArgs& a, const GemmTab& tab, int bits, int out_mode, hipStream_t st) {
+int32_t launch_small_gemm(const GemmArgs& a, const GemmTab& tab, int bits, int out_mode, hipStream_t st, bool* served) {
+  *served = false;
+  if (out_mode != kOutBf16 && out_mode != kOutF32) return RPTQ_OK;
   const bool f32 = out_mode == kOutF32;
-  if (bits == 3) return f32 ? launch_small_out<3, kOutF32>(a, tab, st) : launch_small_out<3, kOutBf16>(a, tab, st);
-  if (bits == 4) return f32 ? launch_small_out<4, kOutF32>(a, tab, st) : launch_small_out<4, kOutBf16>(a, tab, st);
-  return f32 ? launch_small_out<8, kOutF32>(a, tab, st) : launch_small_out<8, kOutBf16>(a, tab, st);
+  if (bits == 3) return f32 ? launch_small_out<3, kOutF32>(a, tab, st, served) : launch_small_out<3, kOutBf16>(a, tab, st, served);
+  if (bits == 4) return f32 ? launch_small_out<4, kOutF32>(a, tab, st, served) : launch_small_out<4, kOutBf16>(a, tab, st, served);
+  return f32 ? launch_small_out<8, kOutF32>(a, tab, st, served) : launch_small_out<8, kOutBf16>(a, tab, st, served);
 }
 
 }  // namespace rptq
