@@ -19,7 +19,9 @@
  *    launch shape) and a status word the offline kernels report bad input through.
  *    Nothing a result depends on.
  *  - The first launch of a shape on a device makes those driver queries and must
- *    therefore happen outside stream capture (RPTQ_ERR_CAPTURE otherwise); every later
+ *    therefore happen outside stream capture (RPTQ_ERR_CAPTURE otherwise; for the products, one
+ *    call of more than 32 rows with the same code and output types stands for all of them, and calls
+ *    of up to 32 rows need none); every later
  *    launch of the online entry points (rptq_ln_quant, rptq_cluster_gemm, rptq_cluster_gemm_quant) makes no
  *    driver call besides the kernel launches, allocates nothing and never synchronizes.
  *  - `stream` is a hipStream_t passed as void*.  Calls are asynchronous on that stream

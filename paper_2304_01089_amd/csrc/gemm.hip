@@ -656,19 +656,31 @@ __global__ void __launch_bounds__(256) rowterm_reduce_kernel(const double* part,
 }
 
 // ---------------------------------------------------------------------------------------------
-template <int BITS, int WGM, int WGN, int WM, int WN, bool PARTIALS, int OUT, bool CWISE>
-static int32_t launch_cfg(const GemmArgs& a, const GemmTab& tab, const GemmQuantOut& qo, float* q_rowterm, hipStream_t st) {
-  constexpr int BM = WGM * WM * 32, BN = WGN * WN * 32;
+// LDS of a workgroup with tiles of BM x BN
+template <int BM, int BN, bool PARTIALS, bool CWISE>
+static constexpr size_t gemm_lds_bytes() {
   constexpr size_t pipe = 2 * kStepSlices * (2 * BM * 16 + kSlicePad);
   constexpr size_t stage = PARTIALS ? 0 : static_cast<size_t>(BM) * (BN + 4) * 4;   // fp32 output tile of the workgroup
   constexpr size_t terms = PARTIALS ? 0 : static_cast<size_t>(3 * BN + BM) * 4;     // output-stage vectors of the tile
   // per-cluster column scales: in the gap between the pipeline buffers and the vectors when it holds them
   constexpr size_t front = pipe > stage ? pipe : stage;
   constexpr size_t cw_bytes = (CWISE && !PARTIALS) ? static_cast<size_t>(32) * BN * 4 : 0;
-  constexpr size_t shmem = front + terms + ((front - pipe >= cw_bytes) ? 0 : cw_bytes);
-  auto kern = cluster_gemm_kernel<BITS, WGM, WGN, WM, WN, PARTIALS, OUT, CWISE>;
+  return front + terms + ((front - pipe >= cw_bytes) ? 0 : cw_bytes);
+}
+
+template <int BITS, int WGM, int WGN, int WM, int WN, bool PARTIALS, int OUT, bool CWISE>
+static int32_t raise_lds_limit(hipStream_t st) {
   static LdsGrant lds_granted;
-  if (int32_t st_lds = ensure_dynamic_lds(reinterpret_cast<const void*>(kern), shmem, &lds_granted, st)) return st_lds;
+  return ensure_dynamic_lds(reinterpret_cast<const void*>(cluster_gemm_kernel<BITS, WGM, WGN, WM, WN, PARTIALS, OUT, CWISE>),
+                            gemm_lds_bytes<WGM * WM * 32, WGN * WN * 32, PARTIALS, CWISE>(), &lds_granted, st);
+}
+
+template <int BITS, int WGM, int WGN, int WM, int WN, bool PARTIALS, int OUT, bool CWISE>
+static int32_t launch_cfg(const GemmArgs& a, const GemmTab& tab, const GemmQuantOut& qo, float* q_rowterm, hipStream_t st) {
+  constexpr int BM = WGM * WM * 32, BN = WGN * WN * 32;
+  constexpr size_t shmem = gemm_lds_bytes<BM, BN, PARTIALS, CWISE>();
+  auto kern = cluster_gemm_kernel<BITS, WGM, WGN, WM, WN, PARTIALS, OUT, CWISE>;
+  if (int32_t st_lds = raise_lds_limit<BITS, WGM, WGN, WM, WN, PARTIALS, OUT, CWISE>(st)) return st_lds;
   GemmArgs b = a;
   b.tiles_n = (a.N + BN - 1) / BN;
   b.tiles_m = static_cast<int32_t>((a.M + BM - 1) / BM);
@@ -689,6 +701,17 @@ static int32_t launch_cfg(const GemmArgs& a, const GemmTab& tab, const GemmQuant
 
 template <int BITS, bool PARTIALS, int OUT, bool CWISE = false>
 static int32_t launch_shape(const GemmArgs& a, const GemmTab& tab, const GemmQuantOut& qo, float* q_rowterm, hipStream_t st) {
+  // Every call of more than 32 rows raises the limit of the 64 x 256 tile, whichever kernel serves it: a program that ran
+  // one such call may record any other.
+  if (!PARTIALS && a.M > 32) {
+    const int32_t s = raise_lds_limit<BITS, 1, 4, 2, 2, PARTIALS, OUT, CWISE>(st);
+    if (s && s != RPTQ_ERR_CAPTURE) return s;               // (while recording: the launch below tells if it needs it)
+  }
+  if constexpr (!PARTIALS && !CWISE && (OUT == kOutBf16 || OUT == kOutF32)) {
+    bool served = false;
+    if (int32_t s = launch_small_gemm(a, tab, BITS, OUT, st, &served)) return s;
+    if (served) return RPTQ_OK;
+  }
   if (a.M <= 32) return launch_cfg<BITS, 1, 4, 1, 1, PARTIALS, OUT, CWISE>(a, tab, qo, q_rowterm, st);
   // 64 x 256 tile; every wave covers all 64 tokens and 64 output channels: each expanded
   // weight fragment feeds two MFMAs and no two waves expand the same weights.  Two such workgroups fill a compute unit,
@@ -806,11 +829,6 @@ int32_t launch_gemm(const void* codes, int64_t M, int32_t bits, const void* Wq, 
   if (quant_out != nullptr) {
     qo = *quant_out;
     out_mode = qo.row_bytes * 8 / N;                        // bits of the codes written
-  }
-  if (cw == nullptr) {
-    bool served = false;
-    if (int32_t s = launch_small_gemm(a, tab, bits, out_mode, st, &served)) return s;
-    if (served) return RPTQ_OK;
   }
   if (bits == 3) return launch_bits<3>(a, tab, out_mode, qo, q_rowterm, st);
   if (bits == 4) return launch_bits<4>(a, tab, out_mode, qo, q_rowterm, st);

@@ -435,7 +435,6 @@ static int32_t launch_small_out(const GemmArgs& a, const GemmTab& tab, hipStream
 
 int32_t launch_small_gemm(const GemmArgs& a, const GemmTab& tab, int bits, int out_mode, hipStream_t st, bool* served) {
   *served = false;
-  if (out_mode != kOutBf16 && out_mode != kOutF32) return RPTQ_OK;
   const bool f32 = out_mode == kOutF32;
   if (bits == 3) return f32 ? launch_small_out<3, kOutF32>(a, tab, st, served) : launch_small_out<3, kOutBf16>(a, tab, st, served);
   if (bits == 4) return f32 ? launch_small_out<4, kOutF32>(a, tab, st, served) : launch_small_out<4, kOutBf16>(a, tab, st, served);
