@@ -16,7 +16,8 @@
  *    calls, per device and behind a lock (calls may come from several host threads and
  *    for several devices): the answers of its one-time driver queries (compute-unit
  *    count, workgroups resident per compute unit and raised dynamic-LDS limit of each
- *    launch shape) and a status word the offline kernels report bad input through.
+ *    launch shape) and the status words the offline kernels report bad input through, one
+ *    per call under way.
  *    Nothing a result depends on.
  *  - The first launch of a shape on a device makes those driver queries and must
  *    therefore happen outside stream capture (RPTQ_ERR_CAPTURE otherwise; for the products, one

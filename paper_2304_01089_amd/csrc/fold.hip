@@ -5,6 +5,9 @@
 // and the per-cluster code sums the integer form of App. A.4 needs.
 #include <hip/hip_runtime.h>
 
+#include <condition_variable>
+#include <mutex>
+
 #include "device_common.h"
 #include "pack_formats.h"
 #include "rptq_internal.h"
@@ -12,10 +15,58 @@
 namespace rptq {
 
 // What the offline kernels report back: bit 0 = a weight is not finite, bit 1 = a row's Eq. 2
-// scale is not a normal fp32 number.  One word per device; cleared and read by launch_fold.
-__device__ int32_t g_fold_status;
+// scale is not a normal fp32 number.  A call owns one of the words from its clearing to its read-back, so
+// that calls from several threads, on several streams, report their own weights.
+constexpr int kStatusWords = 64;
+__device__ int32_t g_fold_status[kStatusWords];
 
-__global__ void fold_status_clear_kernel() { g_fold_status = 0; }
+__global__ void fold_status_clear_kernel(int word) { g_fold_status[word] = 0; }
+
+class StatusWord {
+ public:
+  StatusWord() {                                   // (a 65th call at one time waits for another to end)
+    std::unique_lock<std::mutex> lock(state().mutex);
+    state().freed.wait(lock, [] { return state().taken != ~uint64_t{0}; });
+    word_ = __builtin_ctzll(~state().taken);
+    state().taken |= uint64_t{1} << word_;
+  }
+  ~StatusWord() {
+    {
+      std::lock_guard<std::mutex> lock(state().mutex);
+      state().taken &= ~(uint64_t{1} << word_);
+    }
+    state().freed.notify_one();
+  }
+  StatusWord(const StatusWord&) = delete;
+  StatusWord& operator=(const StatusWord&) = delete;
+  int index() const { return word_; }
+  int32_t clear(hipStream_t st) const {
+    hipLaunchKernelGGL(fold_status_clear_kernel, dim3(1), dim3(1), 0, st, word_);
+    RPTQ_HIP(hipGetLastError());
+    return RPTQ_OK;
+  }
+  // Waits for the stream; RPTQ_ERR_RANGE if the kernels reported anything.
+  int32_t read(hipStream_t st) const {
+    int32_t status = 0;
+    RPTQ_HIP(hipMemcpyFromSymbolAsync(&status, HIP_SYMBOL(g_fold_status), sizeof(status), sizeof(status) * word_,
+                                      hipMemcpyDeviceToHost, st));
+    RPTQ_HIP(hipStreamSynchronize(st));
+    return status ? RPTQ_ERR_RANGE : RPTQ_OK;
+  }
+
+ private:
+  struct State {
+    std::mutex mutex;
+    std::condition_variable freed;
+    uint64_t taken = 0;
+  };
+  static State& state() {
+    static State s;
+    return s;
+  }
+  static_assert(kStatusWords == 64, "a bit each");
+  int word_;
+};
 
 __global__ void fold_ln_kernel(const float* gamma, const float* beta, const int32_t* perm_pad, int32_t k_padded,
                                float* gamma_pad, float* beta_pad) {
@@ -38,6 +89,7 @@ struct FoldArgs {
   int32_t* zW;
   int32_t* wsum;
   float* colterm;
+  int32_t status_word;
 };
 
 struct ScaleTab {
@@ -135,7 +187,7 @@ __global__ void __launch_bounds__(kFoldThreads) fold_weight_kernel(FoldArgs a, C
       for (int c = t; c < geom.k; c += kStep) take(c, a.w_bf16 ? __uint_as_float(static_cast<uint32_t>(wb[c]) << 16) : wf[c]);
     }
   }
-  if (bad) atomicOr(&g_fold_status, 1);
+  if (bad) atomicOr(&g_fold_status[a.status_word], 1);
 #pragma unroll
   for (int m = 32; m >= 1; m >>= 1) {
     lo = fminf(lo, __shfl_xor(lo, m, kWave));
@@ -165,7 +217,7 @@ __global__ void __launch_bounds__(kFoldThreads) fold_weight_kernel(FoldArgs a, C
         zz = -rint((h + l) / (2.0 * s64));
       }
       s32 = static_cast<float>(s64);
-      if (!(s32 >= 1.17549435e-38f && s32 <= 3.4028234664e38f)) atomicOr(&g_fold_status, 2);
+      if (!(s32 >= 1.17549435e-38f && s32 <= 3.4028234664e38f)) atomicOr(&g_fold_status[a.status_word], 2);
       z32 = static_cast<int32_t>(zz);
     }
     sh_inv[my_row] = static_cast<float>(1.0 / static_cast<double>(s32));
@@ -243,6 +295,7 @@ struct FoldCwArgs {
   float* cross_tab;     // [n_padded, g2], position of cluster i: (i & 1) * g2/2 + i/2; holds -sW[o,i] * zW[o,i]
   float* colterm;       // [N]: sum_i sX_i sW[o,i] zX_i wsum[o,i]
   int32_t g2;
+  int32_t status_word;
 };
 
 struct ScaleTabCw {
@@ -309,7 +362,7 @@ __global__ void __launch_bounds__(256) fold_weight_cw_kernel(FoldCwArgs a, Clust
       atomicMax(&k_hi[ci], float_key(hi));
     }
   }
-  if (bad) atomicOr(&g_fold_status, 1);
+  if (bad) atomicOr(&g_fold_status[a.status_word], 1);
   __syncthreads();
   if (tid < g) {                                   // Eq. 2 for block (o, tid)
     const double l = key_float(k_lo[tid]) + 0.0f, h = key_float(k_hi[tid]) + 0.0f;
@@ -324,7 +377,7 @@ __global__ void __launch_bounds__(256) fold_weight_cw_kernel(FoldCwArgs a, Clust
     const float s32 = static_cast<float>(s64);
     // (a block that lies far from zero relative to its width has a large zero point: at most
     // 8 * 2 * 2^24 for fp32 extrema that differ, so it always fits an int32)
-    if (!(s32 >= 1.17549435e-38f && s32 <= 3.4028234664e38f) || !(fabs(zz) <= 1073741824.0)) atomicOr(&g_fold_status, 2);
+    if (!(s32 >= 1.17549435e-38f && s32 <= 3.4028234664e38f) || !(fabs(zz) <= 1073741824.0)) atomicOr(&g_fold_status[a.status_word], 2);
     sh_s[tid] = s32;
     sh_inv[tid] = static_cast<float>(1.0 / static_cast<double>(s32));
     sh_z[tid] = static_cast<int32_t>(zz);
@@ -432,8 +485,9 @@ int32_t launch_fold(const float* gamma, const float* beta, const int32_t* perm_p
   ScaleTab tab;
   for (int i = 0; i < RPTQ_MAX_CLUSTERS; ++i)
     tab.sz[i] = i < geom.g ? static_cast<double>(sX[i]) * static_cast<double>(zX[i]) : 0.0;
-  hipLaunchKernelGGL(fold_status_clear_kernel, dim3(1), dim3(1), 0, st);
-  RPTQ_HIP(hipGetLastError());
+  const StatusWord status;
+  a.status_word = status.index();
+  if (int32_t s = status.clear(st)) return s;
   // As many rows per workgroup as leave two workgroups per compute unit (eight at most: their pieces fill whole
   // cache lines), down to one row, for which the LDS holds every width.
   auto fits = [&](int r) { return fold_lds_layout(r, geom.k, geom.g, geom.k_padded).total <= 80 * 1024 - 256; };
@@ -444,10 +498,7 @@ int32_t launch_fold(const float* gamma, const float* beta, const int32_t* perm_p
   else if (fits(2)) rc = launch_fold_rows<2>(a, geom, tab, st);
   else rc = launch_fold_rows<1>(a, geom, tab, st);
   if (rc) return rc;
-  int32_t status = 0;
-  RPTQ_HIP(hipMemcpyFromSymbolAsync(&status, HIP_SYMBOL(g_fold_status), sizeof(status), 0, hipMemcpyDeviceToHost, st));
-  RPTQ_HIP(hipStreamSynchronize(st));
-  return status ? RPTQ_ERR_RANGE : RPTQ_OK;
+  return status.read(st);
 }
 
 
@@ -480,14 +531,12 @@ int32_t launch_fold_cw(const int32_t* perm_pad_host, const ClusterGeom& geom, co
     tab.sx[i] = i < geom.g ? static_cast<double>(sX[i]) : 0.0;
     tab.zx[i] = i < geom.g ? static_cast<double>(zX[i]) : 0.0;
   }
-  hipLaunchKernelGGL(fold_status_clear_kernel, dim3(1), dim3(1), 0, st);
-  RPTQ_HIP(hipGetLastError());
+  const StatusWord status;
+  a.status_word = status.index();
+  if (int32_t s = status.clear(st)) return s;
   hipLaunchKernelGGL(fold_weight_cw_kernel, dim3(a.n_padded), dim3(256), 0, st, a, geom, tab);
   RPTQ_HIP(hipGetLastError());
-  int32_t status = 0;
-  RPTQ_HIP(hipMemcpyFromSymbolAsync(&status, HIP_SYMBOL(g_fold_status), sizeof(status), 0, hipMemcpyDeviceToHost, st));
-  RPTQ_HIP(hipStreamSynchronize(st));
-  return status ? RPTQ_ERR_RANGE : RPTQ_OK;
+  return status.read(st);
 }
 
 int32_t launch_unpack_weights(const void* Wq, int32_t N, const ClusterGeom& geom, int8_t* out, hipStream_t st) {

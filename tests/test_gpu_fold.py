@@ -71,3 +71,47 @@ def test_fold_reports_bad_weights():
         with pytest.raises(rp.RptqError) as e:
             rp.rptq_fold_reorder(None, None, k, np.arange(k, dtype=np.int32), off, [1.0], [0], W, N, k, None, perm_pad, None, None, Wq, *args)
         assert e.value.status == -6
+
+
+def test_concurrent_folds_report_their_own_weights():
+    """Two threads on two streams, one with a weight that is not finite: only its calls fail."""
+    import threading
+
+    import paper_2304_01089_amd as rp
+    rp.load_library()
+    k, N, rounds = 1024, 4096, 200
+    off = np.array([0, k // 2, k], np.int32)
+    dev = dict(device="cuda")
+    bad_calls, errors = {True: 0, False: 0}, []
+    start = threading.Barrier(2)
+
+    def work(bad):
+        try:
+            stream = torch.cuda.Stream()
+            with torch.cuda.stream(stream):
+                W = torch.full((N, k), 0.5, **dev)
+                if bad:
+                    W[0, 0] = float("nan")
+                perm_pad = torch.zeros(rp.rptq_padded_k(off), dtype=torch.int32, **dev)
+                Wq = torch.zeros(rp.rptq_weight_bytes(N, k), dtype=torch.uint8, **dev)
+                args = (torch.zeros(N, **dev), torch.zeros(N, dtype=torch.int32, **dev),
+                        torch.zeros((N, 2), dtype=torch.int32, **dev), torch.zeros(N, **dev))
+                stream.synchronize()
+                start.wait(30)
+                for _ in range(rounds):
+                    try:
+                        rp.rptq_fold_reorder(None, None, k, np.arange(k, dtype=np.int32), off, [1.0, 1.0], [0, 0], W, N, k, None,
+                                             perm_pad, None, None, Wq, *args)
+                    except rp.RptqError as e:
+                        assert e.status == -6
+                        bad_calls[bad] += 1
+        except BaseException as e:
+            errors.append(e)
+
+    threads = [threading.Thread(target=work, args=(b,)) for b in (True, False)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join(60)
+    assert not errors, errors
+    assert bad_calls == {True: rounds, False: 0}
