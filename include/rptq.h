@@ -88,7 +88,7 @@ typedef enum {
   RPTQ_ERR_RANGE = -6,     /* a zero point or scale is outside what the kernels carry exactly */
   RPTQ_ERR_WORKSPACE = -7, /* workspace too small */
   RPTQ_ERR_HIP = -8,       /* a HIP call failed; see rptq_last_hip_error() */
-  RPTQ_ERR_CAPTURE = -9    /* first launch of this shape on this device while the stream is capturing */
+  RPTQ_ERR_CAPTURE = -9    /* a fold, or the first launch of this shape on this device, while the stream is capturing */
 } rptq_status;
 
 enum { RPTQ_DTYPE_BF16 = 0, RPTQ_DTYPE_F32 = 1 };
@@ -162,7 +162,7 @@ int32_t rptq_calibrate(const void* const* x_batches, const int64_t* rows, int32_
  *  Wq_packed  device out, rptq_weight_bytes(N, K_p)
  *  sW device fp32 [N], zW device int32 [N], wsum device int32 [N,g], colterm device fp32 [N]
  * Offline call: synchronizes the stream before returning (so that it can report what the
- * kernels found), cannot be captured.  RPTQ_ERR_RANGE when a weight is not finite or a row's
+ * kernels found); refused while the stream is capturing (RPTQ_ERR_CAPTURE).  RPTQ_ERR_RANGE when a weight is not finite or a row's
  * range gives a scale that is not a normal fp32 number; the outputs are then unspecified.
  */
 int32_t rptq_fold_reorder(const float* gamma, const float* beta, int32_t d,

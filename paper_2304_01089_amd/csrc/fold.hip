@@ -457,6 +457,8 @@ int32_t launch_fold(const float* gamma, const float* beta, const int32_t* perm_p
                     const float* sX, const int32_t* zX, const void* W, int32_t w_dtype, int32_t N,
                     const int32_t* perm_out_host, int32_t* perm_pad, float* gamma_pad, float* beta_pad,
                     void* Wq_packed, float* sW, int32_t* zW, int32_t* wsum, float* colterm, hipStream_t st) {
+  // (refused before anything is recorded: a graph would keep copies from host arrays that end with this call)
+  if (int32_t s = require_not_capturing(st)) return s;
   // the index arrays were validated on the host; they are uploaded from there, so what the
   // kernels read is what was checked
   RPTQ_HIP(hipMemcpyAsync(perm_pad, perm_pad_host, sizeof(int32_t) * geom.k_padded, hipMemcpyHostToDevice, st));
@@ -506,6 +508,7 @@ int32_t launch_fold_cw(const int32_t* perm_pad_host, const ClusterGeom& geom, co
                        const void* W, int32_t w_dtype, int32_t N, const int32_t* perm_out_host, int32_t* perm_pad,
                        void* Wq_packed, float* sW, int32_t* zW, int32_t* wsum, float* scale_tab, float* cross_tab,
                        float* colterm, hipStream_t st) {
+  if (int32_t s = require_not_capturing(st)) return s;
   RPTQ_HIP(hipMemcpyAsync(perm_pad, perm_pad_host, sizeof(int32_t) * geom.k_padded, hipMemcpyHostToDevice, st));
   // the validated source rows travel in the first zero-point entry of every output row
   if (perm_out_host)

@@ -115,3 +115,35 @@ def test_concurrent_folds_report_their_own_weights():
         t.join(60)
     assert not errors, errors
     assert bad_calls == {True: rounds, False: 0}
+
+
+@pytest.mark.parametrize("cw", [False, True])
+def test_fold_is_not_recorded(cw):
+    """Under stream capture both folds are refused with nothing in the graph (they copy from host arrays and wait)."""
+    import paper_2304_01089_amd as rp
+    rp.load_library()
+    k, N = 4096, 64
+    off = np.array([0, 1000, k], np.int32)
+    dev = dict(device="cuda")
+    W = torch.full((N, k), 0.5, **dev)
+    perm_pad = torch.full((rp.rptq_padded_k(off),), 7, dtype=torch.int32, **dev)
+    Wq = torch.full((rp.rptq_weight_bytes(N, perm_pad.numel()),), 0x5A, dtype=torch.uint8, **dev)
+    sW, zW, wsum = torch.zeros((N, 2), **dev), torch.full((N, 2), 7, dtype=torch.int32, **dev), torch.zeros((N, 2), dtype=torch.int32, **dev)
+    ct, probe = torch.zeros(N, **dev), torch.zeros(1, **dev)
+    tabs = [torch.zeros(n // 4, **dev) for n in (rp.rptq_cw_scale_bytes(N, 2), rp.rptq_cw_cross_bytes(N, 2))]
+    perm = np.arange(k, dtype=np.int32)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        probe.add_(1.0)
+        with pytest.raises(rp.RptqError) as e:
+            if cw:
+                rp.rptq_fold_reorder_cw(perm, off, [1.0, 1.0], [0, 0], W, N, k, np.arange(N, dtype=np.int32), perm_pad, Wq, sW, zW, wsum, *tabs, ct)
+            else:
+                rp.rptq_fold_reorder(None, None, k, perm, off, [1.0, 1.0], [0, 0], W, N, k, np.arange(N, dtype=np.int32), perm_pad,
+                                     None, None, Wq, sW, zW, wsum, ct)
+        assert e.value.status == -9
+    graph.replay()
+    torch.cuda.synchronize()
+    assert probe.item() == 1.0
+    assert (perm_pad == 7).all() and (Wq == 0x5A).all() and (zW == 7).all()
