@@ -86,7 +86,7 @@ __global__ void __launch_bounds__(256) kv_quant_kernel(const uint4* x, int64_t T
     const uint4* p2 = row_ptr(row + 2 * stride);
     nxt0 = p2[ch0];
     nxt1 = p2[ch1];
-    __builtin_amdgcn_wave_barrier();                 // (one wave: LDS executes its instructions in order)
+    wave_lds_fence();
     uint32_t D[4] = {0u, 0u, 0u, 0u};                // biased codes, one byte each
 #pragma unroll
     for (int e = 0; e < kKvLaneCodes; ++e) {
@@ -97,7 +97,7 @@ __global__ void __launch_bounds__(256) kv_quant_kernel(const uint4* x, int64_t T
       if (BITS < 8) b = fminf(b, kUMax);             // upper clamp; the conversion saturates at 0 and 255
       D[e / 4] = __builtin_amdgcn_cvt_pk_u8_f32(b, e & 3, D[e / 4]);
     }
-    __builtin_amdgcn_wave_barrier();
+    wave_lds_fence();
     uint8_t* out = codes + row * out_row_bytes + out_tile;
     if (BITS == 8) {
       const uint4 o = make_uint4(D[0] ^ 0x80808080u, D[1] ^ 0x80808080u, D[2] ^ 0x80808080u, D[3] ^ 0x80808080u);

@@ -484,7 +484,7 @@ __global__ void __launch_bounds__(256) cluster_rowsums_kernel(const uint8_t* cod
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int64_t row = static_cast<int64_t>(blockIdx.x) * 4 + wave;
   if (lane < RPTQ_MAX_CLUSTERS) acc[wave][lane] = 0;
-  __builtin_amdgcn_wave_barrier();
+  wave_lds_fence();
   if (row < M) {
     const int groups = geom.pad_off[geom.g] / kGroup;
     for (int gi = lane; gi < groups; gi += kWave) {
@@ -502,7 +502,7 @@ __global__ void __launch_bounds__(256) cluster_rowsums_kernel(const uint8_t* cod
       atomicAdd(&acc[wave][ci], sum);
     }
   }
-  __builtin_amdgcn_wave_barrier();
+  wave_lds_fence();
   if (row < M && lane < g2) {
     float v = 0.0f;
     if (lane < geom.g) v = static_cast<float>(tab.s[lane] * (static_cast<double>(acc[wave][lane]) - tab.nz[lane]));
