@@ -715,17 +715,18 @@ static int32_t launch_shape(const GemmArgs& a, const GemmTab& tab, const GemmQua
   if (a.M <= 32) return launch_cfg<BITS, 1, 4, 1, 1, PARTIALS, OUT, CWISE>(a, tab, qo, q_rowterm, st);
   // 64 x 256 tile; every wave covers all 64 tokens and 64 output channels: each expanded
   // weight fragment feeds two MFMAs and no two waves expand the same weights.  Two such workgroups fill a compute unit,
-  // 512 the chip: where the first or second round of them is well short of full, a 64 x 128 tile (half the accumulators,
-  // three workgroups per compute unit) fills it better, although it stages the activations twice as often.  us for
-  // 64 x 256 | 64 x 128, by the number of 64 x 256 tiles:
-  //   256 ( 512 x 8192 x 2048) 20.3 | 17.2    512 (2048 x 4096 x 4096) 48.4 | 55.0     768 (2048 x 6144 x  5120)  85.0 |  85.0
-  //   288 (1500 x 3000 x 3000) 32.6 | 25.9    576 (1500 x 6000 x 3000) 49.1 | 42.5     896 (2048 x 7168 x  5120) 103.9 | 110.0
-  //   474 ( 333 x 20000 x 12288) 122 | 122    640 (2048 x 5120 x 5120) 80.9 | 72.7    1024 (2048 x 8192 x  2048)  53.4 |  55.8
+  // 512 the chip.  A 64 x 128 tile (half the accumulators, three workgroups per compute unit: 768, or 384 of the large
+  // tiles, fill the chip) stages the activations twice as often; it is taken where it needs one round for fewer than
+  // 512 tiles, and where the second round of large tiles is well short of full.  us for 64 x 256 | 64 x 128 at K = 5120
+  // (* 3000), by the number of 64 x 256 tiles:
+  //   Y as bf16            352: 51 | 43   384: 50 | 45   416: 52 | 60   576*: 60 | 53   640: 80 | 74    768: 89 | 87
+  //   next site's codes    335: 60 | 53   375: 62 | 56   416: 54 | 63   496: 57 | 66   624*: 66 | 57   656: 85 | 86   864: 103 | 109
+  //   a pair per cluster   320: 65 | 52   384: 64 | 54   416: 66 | 73   576*: 89 | 67   640: 108 | 89   768: 111 | 106
   // (The sums and their order are the same.)
   constexpr int64_t kRound = 512;
   const int64_t tiles = (a.M + 63) / 64 * ((a.N + 255) / 256);
   if constexpr (!PARTIALS)
-    if (tiles <= kRound * 7 / 8 || (tiles > kRound && tiles <= kRound * 11 / 8))
+    if (tiles <= kRound * 3 / 4 || (tiles > kRound && tiles <= kRound * 11 / 8))
       return launch_cfg<BITS, 1, 4, 2, 1, PARTIALS, OUT, CWISE>(a, tab, qo, q_rowterm, st);
   return launch_cfg<BITS, 1, 4, 2, 2, PARTIALS, OUT, CWISE>(a, tab, qo, q_rowterm, st);
 }
