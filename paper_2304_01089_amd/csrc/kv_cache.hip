@@ -123,14 +123,20 @@ __global__ void __launch_bounds__(256) kv_quant_kernel(const uint4* x, int64_t T
 }
 
 // Read-back.  Memory bound (d*bits/8 bytes in, 2d out per row), so the stores decide: a lane expands 8
-// consecutive codes of a row into one 16-byte store, a wave's store is 1 KiB contiguous, and the stores
-// are non-temporal (nothing here reads them again).  Measured at 8192 x 12288, 3 bits: one lane per 32-code
-// group, four 16-byte stores 64 bytes apart, 91 us; this split with ordinary stores 68 us; non-temporal 42 us
-// (5.7 TB/s).  The 8 positions' constants stay in registers; kKvRowsAhead rows are requested while the rows
+// consecutive codes of a row into one 16-byte store, a wave's store is 1 KiB contiguous.  One lane per 32-code group with
+// four 16-byte stores 64 bytes apart took 91 us at 8192 x 12288, 3 bits, this split 68, with non-temporal stores 42 us
+// (5.7 TB/s).  But attention reads the values next, and non-temporal stores send them past the 256 MiB last-level cache:
+// they are used only where the keys and values of a layer together would not stay in it.  us for key and value of one
+// layer, the two read-backs alone and followed by a full read of both, ordinary | non-temporal:
+//    17 MB each   13.8 | 11.8    48 |  50        101 MB   48 | 47   101 | 119
+//    34 MB        23.0 | 19.8    57 |  61        151 MB  110 | 64   211 | 170
+//    67 MB        37.0 | 34.6    79 |  89        201 MB  138 | 84   265 | 254
+// The 8 positions' constants stay in registers; kKvRowsAhead rows are requested while the rows
 // before them are expanded (2, 4 and 8 rows measured the same).
+constexpr int64_t kKvStreamBytes = 128ll << 20;
 constexpr int kKvRowsAhead = 2;
 
-template <int BITS>
+template <int BITS, bool STREAM>
 __global__ void __launch_bounds__(256) kv_dequant_kernel(const uint8_t* codes, int64_t T, int32_t d, const KvPos* pos,
                                                          uint16_t* out, int32_t blocks_per_row) {
   typedef float f2 __attribute__((ext_vector_type(2)));
@@ -189,7 +195,11 @@ __global__ void __launch_bounds__(256) kv_dequant_kernel(const uint8_t* codes, i
       const b2 cv = __builtin_convertvector(pr, b2);
       o[j / 2] = *reinterpret_cast<const uint32_t*>(&cv);
     }
-    if (row < T) __builtin_nontemporal_store(o, reinterpret_cast<u4v*>(lane_dst + row * d));
+    if (row < T) {
+      u4v* dst = reinterpret_cast<u4v*>(lane_dst + row * d);
+      if (STREAM) __builtin_nontemporal_store(o, dst);
+      else *dst = o;
+    }
   };
   uint32_t cur[kKvRowsAhead][ND], nxt[kKvRowsAhead][ND];
   int64_t row = blockIdx.x / blocks_per_row;
@@ -241,9 +251,11 @@ int32_t launch_kv_dequant(const void* codes, int64_t T, int32_t d, const KvPos* 
   const dim3 grid(static_cast<unsigned>(blocks_per_row * rows_par)), block(256);
   const uint8_t* cp = static_cast<const uint8_t*>(codes);
   uint16_t* op = static_cast<uint16_t*>(out);
-  if (bits == 3) hipLaunchKernelGGL(kv_dequant_kernel<3>, grid, block, 0, st, cp, T, d, pos, op, blocks_per_row);
-  else if (bits == 4) hipLaunchKernelGGL(kv_dequant_kernel<4>, grid, block, 0, st, cp, T, d, pos, op, blocks_per_row);
-  else hipLaunchKernelGGL(kv_dequant_kernel<8>, grid, block, 0, st, cp, T, d, pos, op, blocks_per_row);
+  const bool stream = T * d * 2 > kKvStreamBytes;
+  auto go = [&](auto kern) { hipLaunchKernelGGL(kern, grid, block, 0, st, cp, T, d, pos, op, blocks_per_row); };
+  if (bits == 3) stream ? go(kv_dequant_kernel<3, true>) : go(kv_dequant_kernel<3, false>);
+  else if (bits == 4) stream ? go(kv_dequant_kernel<4, true>) : go(kv_dequant_kernel<4, false>);
+  else stream ? go(kv_dequant_kernel<8, true>) : go(kv_dequant_kernel<8, false>);
   RPTQ_HIP(hipGetLastError());
   return RPTQ_OK;
 }

@@ -137,3 +137,28 @@ def test_read_back_at_tile_edges(rp, T, H, dh, bits):
     torch.cuda.synchronize()
     assert np.array_equal(guard[: T * d].view(T, d).float().cpu().numpy(), kvo.kv_dequant(q, ref, 0))
     assert (guard[T * d:] == 7.0).all()
+
+
+@pytest.mark.parametrize("bits", [3, 4, 8])
+def test_read_back_on_both_sides_of_the_streaming_size(rp, bits):
+    """Up to 128 MiB of values ordinary stores, above non-temporal ones: the same values."""
+    H, dh, g, T = 64, 128, 2, 8193
+    d = H * dh
+    rng = np.random.default_rng(bits)
+    lo = -rng.random(d).astype(np.float32) - np.float32(0.1)
+    hi = rng.random(d).astype(np.float32) + np.float32(0.1)
+    ref = kvo.cluster_heads([lo], [hi], H, g, bits, 3)
+    got = rp.rptq_cluster_heads([lo], [hi], H, g, bits, 3)
+    table = torch.empty(rp.rptq_kv_table_bytes(d), dtype=torch.uint8, device="cuda")
+    rp.rptq_kv_tables(got["perm"], got["cluster_off"], got["s"][0], got["inv_s"][0], got["z"][0], d, H, g, table)
+    rows = rng.integers(-(1 << (bits - 1)), 1 << (bits - 1), (64, d)).astype(np.int8)
+    packed = torch.from_numpy(packfmt.pack_groups(rows, bits)).cuda().view(64, -1)
+    packed = packed.repeat(T // 64 + 1, 1)[:T].contiguous()
+    out = torch.full((2, T, d), 7.0, dtype=torch.bfloat16, device="cuda")
+    rp.rptq_kv_dequant(packed, T, d, table, bits, out[0])
+    rp.rptq_kv_dequant(packed, T - 1, d, table, bits, out[1][: T - 1])
+    torch.cuda.synchronize()
+    assert torch.equal(out[0][: T - 1], out[1][: T - 1]) and (out[1][T - 1] == 7.0).all()
+    want = kvo.kv_dequant(rows, ref, 0)
+    assert np.array_equal(out[0][:64].float().cpu().numpy(), want)
+    assert np.array_equal(out[0][T - 65:].float().cpu().numpy(), want[np.arange(T - 65, T) % 64])
