@@ -197,3 +197,31 @@ def test_clusterwise_config3_fc1_sampled(rp):
     err = np.abs(yrows - Y)
     print("configs[3] fc1, per-block weight parameters: max err/tol %.3f" % float((err / tol)[ok].max()))
     assert (err[ok] <= tol[ok]).all()
+
+
+@pytest.mark.parametrize("bits", [3, 4, 8])
+def test_ragged_tiles_of_every_width(rp, bits):
+    """M and N that end inside a tile, on 16 x 26 tiles of 64 x 256 (more than 384: not halved), on 64 x 128 and on
+    32 x 128 tiles: against float64 (first method of App. A.4), and the same outputs from each."""
+    M, N, d, g = 1000, 6403, 136, 5
+    rng = np.random.default_rng(bits)
+    x = rng.standard_normal((64, d)).astype(np.float32) * np.exp(rng.normal(0, 1, d)).astype(np.float32)
+    k1 = rp.calibrate_site([dev_bf16(x)], None, None, EPS, False, g, bits, seed=bits)
+    lin = rp.fold_linear_cw(k1, dev(w.weight_matrix(bits + 60, N, d)))
+    q = rng.integers(-(1 << (bits - 1)), 1 << (bits - 1), (M, d)).astype(np.int64)
+    pc = dev(packfmt.pack_codes(q, k1.cluster_off, bits).reshape(-1))
+    rs = rp.cluster_rowsums(k1, pc, M)
+    wq = torch.empty((N, d), dtype=torch.int8, device="cuda")
+    rp.rptq_unpack_weights(lin.Wq, N, k1.cluster_off, wq)
+    ci = np.repeat(np.arange(k1.g_eff), np.diff(k1.cluster_off))
+    xh = k1.s.astype(np.float64)[ci] * (q - k1.z[ci])
+    wh = lin.sW.cpu().numpy().reshape(N, -1).astype(np.float64)[:, ci] * (wq.cpu().numpy() - lin.zW.cpu().numpy().reshape(N, -1).astype(np.float64)[:, ci])
+    Y = xh @ wh.T
+    for dtype in (torch.float32, torch.bfloat16):
+        y = torch.full((M + 1, N), 7.0, dtype=dtype, device="cuda")
+        rp.cluster_gemm_cw(k1, lin, pc, rs, M, y=y[:M])
+        for m in (300, 31):
+            assert torch.equal(rp.cluster_gemm_cw(k1, lin, pc, rs, m, dtype=dtype), y[:m])
+        assert (y[M] == 7.0).all()
+        got = y[:M].float().cpu().numpy().astype(np.float64)
+        assert (np.abs(got - Y) <= tol_of(Y) + (np.abs(Y) * 2.0 ** -7 if dtype == torch.bfloat16 else 0.0)).all()

@@ -73,6 +73,10 @@ def oracle_codes(H, relu, c2, bits):
     ("a3_to_a3_few_rows", 128, 520, 9, 3, 3, 4, 6, False),
     ("few_rows", 256, 1024, 20, 4, 4, 8, 8, True),        # the weight-streaming launch shape
     ("one_row", 128, 256, 1, 4, 4, 4, 4, True),
+    # 17 x 24 or 25 tiles of 64 x 256 (more than 384: not halved), the last row tile ragged
+    ("large_tile_a4_to_a4", 128, 6000, 1050, 4, 4, 8, 8, True),
+    ("large_tile_a8_to_a3", 128, 6000, 1050, 8, 3, 8, 7, True),
+    ("large_tile_a3_to_a8", 128, 6000, 1050, 3, 8, 8, 8, False),
 ])
 def test_product_quantized_for_next_site(rp, name, d, dff, M, bits, bits2, g, g2, relu):
     seed = 4100 + sum(map(ord, name))

@@ -74,9 +74,9 @@ CASES = {
     # input chunks and four units per thread
     "wide_relu": dict(seed=19, d=24576, M=9, g=8, bits=4, N=32, n_cal=2, cal_rows=16, ln=False, relu=True),
     "one_row": dict(seed=20, d=512, M=1, g=4, bits=3, N=64),
-    # the depth of the large workloads on the 64-token tile (two row tiles, the second ragged; two
-    # column tiles): the int32 accumulators run over all of K without being cleared, so the
-    # literal per-cluster integers are pinned at K = 12288 (3 bit) and K = 20480 (4 bit)
+    # the depth of the large workloads: the literal per-cluster integers at K = 12288 (3 bit) and K = 20480 (4 bit)
+    # come from the 64 x 256 tile (two row tiles, the second ragged; two column tiles), the outputs from the kernel that
+    # splits K
     "deep_a3": dict(seed=21, d=12288, M=72, g=32, bits=3, N=512, n_cal=2, cal_rows=64),
     "deep_relu_a4": dict(seed=22, d=20480, M=72, g=32, bits=4, N=512, n_cal=2, cal_rows=64, ln=False, relu=True),
 }

@@ -16,6 +16,7 @@ torch = pytest.importorskip("torch")
     (33, 4097, 264, 8), (100, 4097, 1032, 32), (32, 32768, 136, 10),                                # K in 4, and not split
     (64, 23040, 72, 8), (333, 4099, 1000, 16), (700, 2047, 2056, 11),
     (65, 15400, 520, 16), (1000, 2049, 1000, 8), (2100, 4500, 200, 9),                              # not split, 64 x 128 tiles
+    (1000, 6401, 200, 9), (2100, 5700, 200, 9), (1000, 6403, 136, 3),                               # 416 and 759 tiles of 64 x 256
     (33, 70, 600, 7),
 ])
 def test_split_product_against_float64(M, N, d, g, bits):
