@@ -629,7 +629,7 @@ __global__ void __launch_bounds__(256, 2) cluster_gemm_kernel(GemmArgs a, GemmTa
 
 // Sum over the column tiles of the row sums the quantizing output stage left: 16 rows per workgroup, 16
 // threads per row, each adding every 16th tile in tile order; the 16 sums are added in order.  (One thread per
-// row is a serial chain of loads: 5.5 us for 166 tiles x 32 rows against 3 us.)
+// row is a serial chain of loads: 5.5 us for 166 tiles x 32 rows against 3.8 us.)
 __global__ void __launch_bounds__(256) rowterm_reduce_kernel(const double* part, int tiles_n, int64_t M, float* rowterm) {
   __shared__ double sums[16][17];
   const int r = threadIdx.x & 15, j0 = threadIdx.x >> 4;

@@ -419,15 +419,19 @@ static int32_t launch_small_cfg(const GemmArgs& a, const GemmTab& tab, int lds_b
 //   128 x  3072 x   768 (T 384)   6.9 |  8.7 |  5.8     8.6 | 10.8 |  8.9    12.2 | 15.3 | 12.1
 //    64 x  5120 x  5120 (T 320)  16.4 | 13.4 |  9.7    18.3 | 15.2 | 11.4    21.2 | 19.6 | 16.1
 //    16 x 16384 x 12288 (T 512)  26.8 | 19.2 | 19.1    28.0 | 23.7 | 19.6    29.8 | 26.9 | 23.2
+//    64 x 12288 x  8192 (T 768)  23.9 |      | 22.2    25.9 |      | 25.1    28.8 |      | 34.6
+//    64 x 16000 x  5120 (T 1000) 17.3 |      | 19.2    19.3 |      | 22.7    22.3 |      | 30.9
 // Eight ranges fill the chip with one workgroup per compute unit (T up to 256), four with two.  What a split costs is the
-// chain, by the cluster; beyond 256 tiles, where less is gained, it pays from four slices per cluster on average.
+// chain, by the cluster; beyond 256 tiles, where less is gained, it pays from 2.5 slices per cluster on average, against
+// the weight-streaming kernel (up to 32 rows) from four (2.5 at 32 x 12288 x 2048 and 64 x 8192 x 2048, 32 clusters:
+// 10.7 | 13.4 and 14.8 | 13.6; 2 at 128 x 3072 x 768, 16 clusters; 4.5 at 32 x 12288 x 2048, 16 clusters).
 template <int BITS, int OUT>
 static int32_t launch_small_out(const GemmArgs& a, const GemmTab& tab, hipStream_t st, bool* served) {
   const int64_t tiles = (a.M + kSmallTile - 1) / kSmallTile * ((a.N + kSmallTile - 1) / kSmallTile);
   if (tiles <= 256)
     return a.M <= 16 ? launch_small_cfg<BITS, 8, 16, OUT>(a, tab, 160 * 1024, st, served)
                      : launch_small_cfg<BITS, 8, 32, OUT>(a, tab, 160 * 1024, st, served);
-  if (tiles <= 512 && a.used_slices >= 4 * tab.g)
+  if (tiles <= 512 && 2 * a.used_slices >= (a.M > 32 ? 5 : 8) * tab.g)
     return a.M <= 16 ? launch_small_cfg<BITS, 4, 16, OUT>(a, tab, 80 * 1024, st, served)
                      : launch_small_cfg<BITS, 4, 32, OUT>(a, tab, 80 * 1024, st, served);
   return RPTQ_OK;
