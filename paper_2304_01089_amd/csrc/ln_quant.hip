@@ -15,44 +15,11 @@
 #include <type_traits>
 
 #include "device_common.h"
+#include "ln_common.h"
 #include "pack_formats.h"
 #include "rptq_internal.h"
 
 namespace rptq {
-
-// 16 bytes as a plain vector value (copies of the runtime's uint4 struct are memory copies, which can keep
-// register arrays in scratch memory)
-typedef unsigned u4v __attribute__((ext_vector_type(4)));
-
-struct LnQuantArgs {
-  const uint4* x;          // bf16 [M, d], 8 values per uint4
-  int64_t M;
-  int32_t d;
-  int32_t chunks;          // d / 8
-  const float* gamma_pad;
-  const float* beta_pad;
-  float eps;
-  int32_t relu;
-  const int32_t* perm_pad;
-  uint8_t* codes;
-  float* rowterm;
-  int32_t n_units;         // K_p / codes-per-unit
-  int32_t row_bytes;       // K_p * bits / 8
-  int32_t ring;            // row buffers in LDS: 3, or 2 (one more barrier per row) when three do not fit
-};
-
-template <int BITS>
-struct Unit {
-  static constexpr int kCodes = (BITS == 3) ? 16 : 8;
-};
-
-// Position inside its 32-group of local code e of a 3-bit unit with the given role.
-// role 0 carries codes 0..7, 24..27, 16..19; role 1 carries 8..15, 28..31, 20..23.
-__device__ __forceinline__ int pos3(int role, int e) {
-  if (e < 8) return role * 8 + e;
-  if (e < 12) return 24 + role * 4 + (e - 8);
-  return 16 + role * 4 + (e - 12);
-}
 
 // LDS: `ring` row buffers (bf16 row + a 16-byte slot for surplus lanes), then per parity the
 // partial sums of the unit threads ({S1, S2} and the de-quantized row sum), then per parity
@@ -367,27 +334,7 @@ __global__ void __launch_bounds__(1024) ln_quant_kernel(LnQuantArgs a, ClusterGe
       const double part = sdq[n] * static_cast<double>(static_cast<int32_t>(usum) + usum_fix[n]);
       rt += unit_ok[n] ? part : 0.0;
 
-      if (BITS == 8) {
-        uint2 o;
-        o.x = D[0] ^ 0x80808080u;
-        o.y = D[1] ^ 0x80808080u;
-        if (unit_ok[n]) *reinterpret_cast<uint2*>(out_row + out_off[n]) = o;
-      } else if (BITS == 4) {
-        const uint32_t o = ((D[0] << 4) | D[1]) ^ 0x88888888u;
-        if (unit_ok[n]) *reinterpret_cast<uint32_t*>(out_row + out_off[n]) = o;
-      } else {
-        // role 0 -> x0 and its half of x2; role 1 -> x1 and its half of x2 (partner = lane ^ 1)
-        const uint32_t w1 = ((D[0] << 5) | (D[1] << 2) | ((D[2] >> 1) & 0x03030303u)) ^ 0x80808080u ^ 0x10101010u ^ 0x02020202u;
-        const int role = tid & 1;
-        const uint32_t mine = role ? (((D[3] << 2) ^ 0x10101010u) | ((D[2] & 0x01010101u) << 1))
-                                   : (((D[3] << 5) ^ 0x80808080u) | (D[2] & 0x01010101u));
-        const uint32_t other = __shfl_xor(mine, 1, kWave);
-        if (unit_ok[n]) {
-          uint32_t* p = reinterpret_cast<uint32_t*>(out_row + out_off[n]);
-          p[0] = w1;
-          if (role) p[1] = mine | other;
-        }
-      }
+      store_unit<BITS>(D, tid & 1, unit_ok[n], out_row + out_off[n]);
     }
     part3[static_cast<size_t>(i & 1) * TU + tid] = rt;
     if (BC >= 0) return;
@@ -531,12 +478,16 @@ static int32_t launch_kernel(const LnQuantArgs& a, const ClusterGeom& geom, cons
                              int64_t want_grid, int lds_per_cu, size_t shmem, hipStream_t st) {
   auto kern = ln_quant_kernel<BITS, NUNIT, NCH, LN, FIXED>;
   static LdsGrant lds_granted;
-  if (int32_t st_lds = ensure_dynamic_lds(reinterpret_cast<const void*>(kern), shmem, &lds_granted, st)) return st_lds;
   // workgroups resident per compute unit (registers, threads, LDS); the grid is one full round
   static OccupancyMemo occupancy;
   int per_cu = 1;
+  // (both are asked for before the choice of kernel: one call of few rows stands for a recorded call of many)
+  if (int32_t st_lds = ensure_dynamic_lds(reinterpret_cast<const void*>(kern), shmem, &lds_granted, st)) return st_lds;
   if (int32_t st_occ = resident_workgroups(reinterpret_cast<const void*>(kern), threads, shmem, &occupancy, st, &per_cu))
     return st_occ;
+  bool served = false;
+  if (int32_t s = launch_ln_rows(a, geom, qt, BITS, NUNIT, NCH, threads - kWave, static_cast<int>(want_grid), st, &served)) return s;
+  if (served) return RPTQ_OK;
   (void)lds_per_cu;
   const int64_t grid = std::min<int64_t>(a.M, want_grid * per_cu);
   hipLaunchKernelGGL(kern, dim3(static_cast<unsigned>(grid)), dim3(threads), shmem, st, a, geom, qt);
