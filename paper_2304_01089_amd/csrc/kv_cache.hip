@@ -38,6 +38,12 @@ __global__ void __launch_bounds__(256) kv_quant_kernel(const uint4* x, int64_t T
                                                        uint8_t* codes, int32_t segs, int32_t row_groups) {
   constexpr int kQMin = -(1 << (BITS - 1));
   constexpr float kUMax = static_cast<float>((1 << BITS) - 1);
+  // The tile's table records, read by the whole workgroup in order.  (A lane's 16 records are 256 bytes of their own:
+  // requested by the lanes that need them, every request touches 64 cache lines, and that was most of the time of few rows:
+  // 16 x 2048 5.6 -> 3.1 us, 1000 x 2048 9.4 -> 4.5, 1000 x 12288 16.4 -> 12.3, 8192 x 12288 46 -> 42.)  16 bytes follow
+  // every lane's records, so that eight lanes read from different banks.
+  constexpr int kLaneTab = kKvLaneCodes * 16 + 16;
+  __shared__ __align__(16) unsigned char tab[kWave * kLaneTab];
   __shared__ __align__(16) unsigned char lds[4][kKvTile * 2];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int seg = blockIdx.x % segs, rg = blockIdx.x / segs;
@@ -45,24 +51,12 @@ __global__ void __launch_bounds__(256) kv_quant_kernel(const uint4* x, int64_t T
   const int n_here = (d - base_ch) < kKvTile ? (d - base_ch) : kKvTile;      // channels of this tile (multiple of 32)
   unsigned char* my = lds[wave];
 
-  // per-lane constants: source offset inside the tile, 1/s and the biased zero point of each code
-  uint32_t src[kKvLaneCodes];
-  float inv_s[kKvLaneCodes], zbf[kKvLaneCodes];
-#pragma unroll
-  for (int e = 0; e < kKvLaneCodes; ++e) {
-    const int lp = kv_local_pos<BITS>(lane, e);
-    const KvPos kp = pos[base_ch + (lp < n_here ? lp : 0)];
-    src[e] = static_cast<uint32_t>(kp.src - base_ch) * 2u;
-    inv_s[e] = kp.inv_s;
-    zbf[e] = static_cast<float>(kp.z - kQMin);
-  }
   const bool lane_ok = (BITS == 3) ? ((lane >> 1) * kGroup < n_here) : (lane * kKvLaneCodes < n_here);
   // this lane's two 16-byte chunks of the tile's input (clamped inside the tile; surplus data is never gathered)
   const int chunks_here = n_here / 8;
   const int64_t row_chunks = d / 8;
   const int64_t stride = static_cast<int64_t>(row_groups) * 4;
   int64_t row = static_cast<int64_t>(rg) * 4 + wave;
-  if (row >= T) return;
   const int64_t out_row_bytes = static_cast<int64_t>(d) * BITS / 8;
   const int64_t out_tile = static_cast<int64_t>(base_ch) * BITS / 8;
 
@@ -74,10 +68,29 @@ __global__ void __launch_bounds__(256) kv_quant_kernel(const uint4* x, int64_t T
     if (r >= T) r = T - 1;
     return x + r * row_chunks + base_ch / 8;
   };
+  // (requested before the table, so that the two latencies run side by side)
   const uint4* p0 = row_ptr(row);
   uint4 cur0 = p0[ch0], cur1 = p0[ch1];
   const uint4* p1 = row_ptr(row + stride);
   uint4 nxt0 = p1[ch0], nxt1 = p1[ch1];
+  typedef unsigned u4v __attribute__((ext_vector_type(4)));
+#pragma unroll
+  for (int k = 0; k < kKvTile / 256; ++k) {
+    const int i = k * 256 + static_cast<int>(threadIdx.x);
+    *reinterpret_cast<u4v*>(tab + i * 16 + i / kKvLaneCodes * 16) = reinterpret_cast<const u4v*>(pos)[base_ch + (i < n_here ? i : 0)];
+  }
+  __syncthreads();
+  // per-lane constants: source offset inside the tile, 1/s and the biased zero point of each code
+  uint32_t src[kKvLaneCodes];
+  float inv_s[kKvLaneCodes], zbf[kKvLaneCodes];
+#pragma unroll
+  for (int e = 0; e < kKvLaneCodes; ++e) {
+    const int lp = kv_local_pos<BITS>(lane, e);
+    const KvPos kp = *reinterpret_cast<const KvPos*>(tab + lp * 16 + lp / kKvLaneCodes * 16);
+    src[e] = static_cast<uint32_t>(kp.src - base_ch) * 2u;
+    inv_s[e] = kp.inv_s;
+    zbf[e] = static_cast<float>(kp.z - kQMin);
+  }
   for (; row < T; row += stride) {
     *reinterpret_cast<uint4*>(my + lane * 16) = cur0;
     *reinterpret_cast<uint4*>(my + (64 + lane) * 16) = cur1;
@@ -143,15 +156,14 @@ __global__ void __launch_bounds__(256) kv_dequant_kernel(const uint8_t* codes, i
   typedef __bf16 b2 __attribute__((ext_vector_type(2)));
   typedef unsigned u4v __attribute__((ext_vector_type(4)));
   constexpr int ND = (BITS == 3) ? 3 : BITS / 4;       // dwords a lane reads per row
-  const int u = static_cast<int>(blockIdx.x % blocks_per_row) * 256 + static_cast<int>(threadIdx.x);   // unit of 8 codes, the same for every row
-  if (u >= d / 8) return;
-  float s[8], zf[8];
-#pragma unroll
-  for (int j = 0; j < 8; ++j) {
-    const KvPos kp = pos[u * 8 + j];
-    s[j] = kp.s;
-    zf[j] = static_cast<float>(kp.z);
-  }
+  // (s, z) of the workgroup's 2048 positions: the table is read in order and changes threads in LDS, as in kv_quant.  (us
+  // for rows x channels, each thread reading its own 128 bytes of table | this: 4096 x 2048 6.9 | 5.9, 1000 x 5120 at 8 bits
+  // 6.0 | 4.8, 2000 x 12288 at 3 bits 14.5 | 11.6, 8192 x 12288 41.6 | 39.3.)  16 bytes follow every thread's 64.
+  typedef unsigned u2v __attribute__((ext_vector_type(2)));
+  __shared__ __align__(16) unsigned char tab[256 * 80];
+  const int u0 = static_cast<int>(blockIdx.x % blocks_per_row) * 256;
+  const int u_here = u0 + static_cast<int>(threadIdx.x);
+  const int u = u_here < d / 8 ? u_here : d / 8 - 1;      // unit of 8 codes, the same for every row
   const int64_t row_bytes = static_cast<int64_t>(d) * BITS / 8;
   const int64_t stride = gridDim.x / blocks_per_row;
   const int k3 = u & 3;                                // 3-bit: which quarter of the 32-code group
@@ -164,6 +176,28 @@ __global__ void __launch_bounds__(256) kv_dequant_kernel(const uint8_t* codes, i
 #pragma unroll
     for (int k = 0; k < ND; ++k) w[k] = p[k];
   };
+  uint32_t cur[kKvRowsAhead][ND], nxt[kKvRowsAhead][ND];
+  int64_t row = blockIdx.x / blocks_per_row;
+  // (requested before the table, so that the two latencies run side by side)
+#pragma unroll
+  for (int k = 0; k < kKvRowsAhead; ++k) load_row(row + k * stride, cur[k]);
+#pragma unroll
+  for (int k = 0; k < 8; ++k) {
+    const int i = k * 256 + static_cast<int>(threadIdx.x);
+    const u4v rec = reinterpret_cast<const u4v*>(pos)[min(u0 * 8 + i, d - 1)];
+    *reinterpret_cast<u2v*>(tab + i * 8 + i / 8 * 16) = u2v{rec[2], rec[3]};
+  }
+  __syncthreads();
+  if (u_here >= d / 8) return;
+  float s[8], zf[8];
+#pragma unroll
+  for (int j = 0; j < 8; j += 2) {
+    const u4v r2 = *reinterpret_cast<const u4v*>(tab + threadIdx.x * 80 + j * 8);
+    s[j] = __uint_as_float(r2[0]);
+    zf[j] = static_cast<float>(static_cast<int>(r2[1]));
+    s[j + 1] = __uint_as_float(r2[2]);
+    zf[j + 1] = static_cast<float>(static_cast<int>(r2[3]));
+  }
   auto store_row = [&](int64_t row, const uint32_t (&w)[ND]) {
     int q[8];
     if constexpr (BITS == 8) {
@@ -201,10 +235,6 @@ __global__ void __launch_bounds__(256) kv_dequant_kernel(const uint8_t* codes, i
       else *dst = o;
     }
   };
-  uint32_t cur[kKvRowsAhead][ND], nxt[kKvRowsAhead][ND];
-  int64_t row = blockIdx.x / blocks_per_row;
-#pragma unroll
-  for (int k = 0; k < kKvRowsAhead; ++k) load_row(row + k * stride, cur[k]);
   for (; row < T; row += kKvRowsAhead * stride) {
 #pragma unroll
     for (int k = 0; k < kKvRowsAhead; ++k) load_row(row + (kKvRowsAhead + k) * stride, nxt[k]);
