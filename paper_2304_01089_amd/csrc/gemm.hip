@@ -712,7 +712,17 @@ static int32_t launch_shape(const GemmArgs& a, const GemmTab& tab, const GemmQua
     if (int32_t s = launch_small_gemm(a, tab, BITS, OUT, st, &served)) return s;
     if (served) return RPTQ_OK;
   }
-  if (a.M <= 32) return launch_cfg<BITS, 1, 4, 1, 1, PARTIALS, OUT, CWISE>(a, tab, qo, q_rowterm, st);
+  // 32 x 128 tile: decoding, and products whose tiles of that shape do not go round more than three times per compute unit:
+  // with larger ones part of the chip idles and a wave has no other to run beside.  Each weight is expanded for 32 tokens
+  // instead of 64, which is what the larger tiles are ahead by from then on.  us for the rule below | 32 x 128 by the number
+  // of 32 x 128 tiles, g = 32 (* 16):
+  //   Y, K = 5120          280: 21.4 | 18.6   640: 26.9 | 24.0   768: 27.1 | 25.1   896: 27.9 | 30.3   1024: 29.0 | 31.8
+  //   Y, K = 12288         512: 39.6 | 34.3   640: 49.2 | 43.4   768: 49.9 | 46.5   896: 52.0 | 56.8   1024: 54.6 | 60.6
+  //   Y, K = 2048*         512: 11.9 | 10.8   640: 14.5 | 13.0   768: 14.6 | 13.1   896: 14.8 | 15.7   1024: 15.0 | 16.1
+  //   next site's codes    576: 31.5 | 28.3   576*: 18.5 | 16.9   832: 31.8 | 34.2   884*: 20.8 | 23.1
+  //   a pair per cluster   320: 27.6 | 23.3   512: 27.8 | 23.6   768: 36.3 | 32.8   1024: 37.9 | 39.1
+  if (a.M <= 32 || (!PARTIALS && (a.M + 31) / 32 * ((a.N + 127) / 128) <= 768))
+    return launch_cfg<BITS, 1, 4, 1, 1, PARTIALS, OUT, CWISE>(a, tab, qo, q_rowterm, st);
   // 64 x 256 tile; every wave covers all 64 tokens and 64 output channels: each expanded
   // weight fragment feeds two MFMAs and no two waves expand the same weights.  Two such workgroups fill a compute unit,
   // 512 the chip.  A 64 x 128 tile (half the accumulators, three workgroups per compute unit: 768, or 384 of the large

@@ -1,0 +1,31 @@
+"""Both sides of the rule that gives a product 32 x 128 tiles (up to 768 of them): a token's outputs are the same, bit for
+bit, whichever tile its call runs on.  (Each kernel is checked against the oracle elsewhere.)"""
+import pytest
+
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+
+
+@pytest.mark.parametrize("bits", [3, 4, 8])
+@pytest.mark.parametrize("M,N", [(1024, 3064), (2017, 1528), (96, 32760)])
+def test_outputs_do_not_depend_on_the_tile(M, N, bits):
+    import paper_2304_01089_amd as rp
+    d, g, dev = 328, 9, dict(device="cuda")
+    gen = torch.Generator(device="cuda").manual_seed(M + N + bits)
+    more = M + 32 * 400                                        # (well past 768 tiles)
+    x = (torch.randn(more, d, generator=gen, **dev) * torch.exp(torch.randn(d, generator=gen, **dev))).bfloat16()
+    cal = rp.calibrate_site([x[:256]], None, None, 1e-5, False, g, bits, seed=1)
+    W = 0.02 * torch.randn(N, d, generator=gen, **dev)
+    codes, _, rt = rp.ln_quant(cal, x, 1e-5)
+    lin = rp.fold_linear(cal, W)
+    for dtype in (torch.bfloat16, torch.float32):
+        assert torch.equal(rp.cluster_gemm(cal, lin, codes, rt, M, dtype=dtype), rp.cluster_gemm(cal, lin, codes, rt, more, dtype=dtype)[:M])
+    cw, sums = rp.fold_linear_cw(cal, W), rp.cluster_rowsums(cal, codes, more)
+    assert torch.equal(rp.cluster_gemm_cw(cal, cw, codes, sums, M), rp.cluster_gemm_cw(cal, cw, codes, sums, more)[:M])
+    nxt = rp.calibrate_site([(x[:256].float() @ W.T).bfloat16()], None, None, 1e-5, True, g, bits, seed=2)
+    fused = rp.fold_linear(cal, W, next_site=nxt)
+    c0, r0 = rp.cluster_gemm_quant(cal, fused, codes, rt, M, nxt)
+    c1, r1 = rp.cluster_gemm_quant(cal, fused, codes, rt, more, nxt)
+    assert torch.equal(c0, c1[: c0.numel()])
+    # (fp64 sums per column tile of 128 or 256, rounded once to fp32)
+    torch.testing.assert_close(r0, r1[:M], rtol=2.0 ** -23, atol=0.0)
