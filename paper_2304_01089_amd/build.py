@@ -5,12 +5,14 @@ import os
 import shutil
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 LIB = os.path.join(PKG, "librptq.so")
+CALLS = os.path.join(PKG, "_calls.so")          # the binding's native argument marshalling (csrc/calls.cpp)
 SOURCES = ["host.cpp", "api.cpp", "calib_minmax.hip", "fold.hip", "ln_quant.hip", "ln_rows.hip", "gemm.hip", "gemm_small.hip", "kv_cache.hip", "ln_scatter.hip", "method1.hip"]
 
 FLAGS = [
@@ -43,6 +45,18 @@ def _compile(src: str, objdir: str, verbose: bool) -> str:
     return obj
 
 
+def build_calls() -> str:
+    """Compile the CPython module beside the library (host code only)."""
+    tmp = CALLS + ".tmp"
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-I", os.path.join(ROOT, "include"),
+           "-I", sysconfig.get_paths()["include"], os.path.join(CSRC, "calls.cpp"), "-o", tmp]
+    res = subprocess.run(cmd, capture_output=True, text=True)
+    if res.returncode != 0:
+        raise RuntimeError("g++ failed for calls.cpp:\n%s\n%s" % (res.stdout, res.stderr))
+    os.replace(tmp, CALLS)
+    return CALLS
+
+
 def build_library(verbose: bool = False, jobs: int = 6) -> str:
     """Compile every source for gfx950 and link the shared library; returns its path."""
     objdir = os.path.join(PKG, "_build")
@@ -56,6 +70,7 @@ def build_library(verbose: bool = False, jobs: int = 6) -> str:
     if res.returncode != 0:
         raise RuntimeError("link failed:\n%s\n%s" % (res.stdout, res.stderr))
     os.replace(tmp, lib)
+    build_calls()
     return lib
 
 

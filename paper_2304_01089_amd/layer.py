@@ -98,23 +98,24 @@ def fold_linear(cal: Calibration, W, perm_out=None, next_site: Optional[Calibrat
 
 
 def ln_quant(cal: Calibration, x, eps=1e-5, relu=False, codes=None, xsum=None, rowterm=None, want_xsum=False):
-    import torch
     M = x.shape[0]
-    dev = x.device
-    if codes is None:
-        codes = torch.empty(B.rptq_codes_bytes(M, cal.k_padded, cal.bits), dtype=torch.uint8, device=dev)
-    if rowterm is None:
-        rowterm = torch.empty(M, dtype=torch.float32, device=dev)
-    if xsum is None and want_xsum:
-        xsum = torch.empty((M, cal.g_eff), dtype=torch.int32, device=dev)
+    if codes is None or rowterm is None or (xsum is None and want_xsum):
+        import torch
+        dev = x.device
+        if codes is None:
+            codes = torch.empty(B.rptq_codes_bytes(M, cal.k_padded, cal.bits), dtype=torch.uint8, device=dev)
+        if rowterm is None:
+            rowterm = torch.empty(M, dtype=torch.float32, device=dev)
+        if xsum is None and want_xsum:
+            xsum = torch.empty((M, cal.g_eff), dtype=torch.int32, device=dev)
     B.rptq_ln_quant(x, M, cal.d, cal.gamma_pad, cal.beta_pad, eps, relu, cal.perm_pad, cal.cluster_off,
                     cal.s, cal.inv_s, cal.z, cal.bits, codes, xsum, rowterm)
     return codes, xsum, rowterm
 
 
 def cluster_gemm(cal: Calibration, lin: FoldedLinear, codes, rowterm, M, y=None, dtype=None):
-    import torch
     if y is None:
+        import torch
         y = torch.empty((M, lin.N), dtype=dtype or torch.bfloat16, device=codes.device)
     B.rptq_cluster_gemm(codes, M, cal.bits, lin.Wq, lin.N, cal.cluster_off, cal.s, lin.sW, lin.zW, lin.colterm,
                         rowterm, y)
@@ -124,14 +125,15 @@ def cluster_gemm(cal: Calibration, lin: FoldedLinear, codes, rowterm, M, y=None,
 def cluster_gemm_quant(cal: Calibration, lin: FoldedLinear, codes, rowterm, M, next_site: Calibration, relu=True,
                        next_codes=None, next_rowterm=None, workspace=None):
     """The product of `lin` (folded with next_site=...) quantized for `next_site` in the output stage."""
-    import torch
-    dev = codes.device
-    if next_codes is None:
-        next_codes = torch.empty(B.rptq_codes_bytes(M, next_site.k_padded, next_site.bits), dtype=torch.uint8, device=dev)
-    if next_rowterm is None:
-        next_rowterm = torch.empty(M, dtype=torch.float32, device=dev)
-    if workspace is None:
-        workspace = torch.empty(max(16, B.rptq_cluster_gemm_quant_workspace_bytes(M, lin.N)), dtype=torch.uint8, device=dev)
+    if next_codes is None or next_rowterm is None or workspace is None:
+        import torch
+        dev = codes.device
+        if next_codes is None:
+            next_codes = torch.empty(B.rptq_codes_bytes(M, next_site.k_padded, next_site.bits), dtype=torch.uint8, device=dev)
+        if next_rowterm is None:
+            next_rowterm = torch.empty(M, dtype=torch.float32, device=dev)
+        if workspace is None:
+            workspace = torch.empty(max(16, B.rptq_cluster_gemm_quant_workspace_bytes(M, lin.N)), dtype=torch.uint8, device=dev)
     B.rptq_cluster_gemm_quant(codes, M, cal.bits, lin.Wq, lin.N, cal.cluster_off, cal.s, lin.sW, lin.zW, lin.colterm,
                               rowterm, relu, next_site.cluster_off, next_site.s, next_site.inv_s, next_site.z,
                               next_site.bits, next_codes, next_rowterm, workspace)
@@ -170,16 +172,16 @@ def fold_linear_cw(cal: Calibration, W, perm_out=None) -> FoldedLinearCw:
 
 
 def cluster_rowsums(cal: Calibration, codes, M, rowsums=None):
-    import torch
     if rowsums is None:
+        import torch
         rowsums = torch.empty(max(4, B.rptq_cw_rowsum_bytes(M, cal.g_eff) // 4), dtype=torch.float32, device=codes.device)
     B.rptq_cluster_rowsums(codes, M, cal.bits, cal.cluster_off, cal.s, cal.z, rowsums)
     return rowsums
 
 
 def cluster_gemm_cw(cal: Calibration, lin: FoldedLinearCw, codes, rowsums, M, y=None, dtype=None):
-    import torch
     if y is None:
+        import torch
         y = torch.empty((M, lin.N), dtype=dtype or torch.bfloat16, device=codes.device)
     B.rptq_cluster_gemm_cw(codes, M, cal.bits, lin.Wq, lin.N, cal.cluster_off, lin.scale_tab, lin.cross_tab, lin.colterm,
                            rowsums, y)
