@@ -190,6 +190,7 @@ int32_t rptq_fold_reorder(const float* gamma, const float* beta, int32_t d,
  *  xsum       device int32 [M,g] out or NULL: per-cluster code sums
  *  rowterm    device fp32 [M] out or NULL: sum_i s_i (xsum[t,i] - n_i z_i), the row sum of
  *             the de-quantized activation, which the product's zero-point term needs
+ * The codes and the row sum of a row do not depend on the M of the call: every sum is added in the same order.
  * Inputs must be finite: a NaN or infinity in x gives unspecified codes for its row (no
  * fault, no error).
  * Shapes the kernel does not cover return RPTQ_ERR_SHAPE before anything is launched: a

@@ -4,9 +4,11 @@
 // A workgroup takes R rows at once and is done.  The pipelined kernel walks one row per barrier, which hides
 // everything behind the row loop when there is one; with one to four rows per workgroup its chain of waits is the time:
 // tables, constants, row, partial sums, statistics wave, gather, row sum.  Here all loads (rows, per-position constants,
-// one lane-wise read of the cluster tables) are requested at once, every wave reduces its own sums with cross-lane
-// swaps, all waves derive the statistics of the R rows side by side (a row per 16 lanes) so that no result is handed
-// back through a second barrier, and the barriers wait for LDS only, not for loads or stores in flight.
+// one lane-wise read of the cluster tables) are requested at once, the R rows' sums are added up by a wave each while
+// the other waves lay out their constants, and the barriers wait for LDS only, not for loads or stores in flight.
+//
+// Every sum is added in the order of the pipelined kernel (per lane over the waves, then over the lanes), so that a row
+// leaves with the same codes and the same row sum, bit for bit, whichever kernel its call runs on.
 #include <hip/hip_runtime.h>
 
 #include "device_common.h"
@@ -24,22 +26,6 @@ struct LnRowsTab {
   int32_t zb[RPTQ_MAX_CLUSTERS];           // z - qmin
 };
 
-// Sums of four values over the wave; the 16 lanes of DPP row k end with the sum of v_k.  Two swaps halve the number
-// of values while they add lanes up (21 instructions for four sums instead of 72).
-__device__ __forceinline__ double swap_add(double a, double b, bool half) {
-  const uint64_t x = static_cast<uint64_t>(__double_as_longlong(a)), y = static_cast<uint64_t>(__double_as_longlong(b));
-  const uint32_t xl = static_cast<uint32_t>(x), xh = static_cast<uint32_t>(x >> 32);
-  const uint32_t yl = static_cast<uint32_t>(y), yh = static_cast<uint32_t>(y >> 32);
-  // half: lanes 32..63 of a and 0..31 of b change places; else odd rows of a and even rows of b
-  const auto lo = half ? __builtin_amdgcn_permlane32_swap(xl, yl, false, false) : __builtin_amdgcn_permlane16_swap(xl, yl, false, false);
-  const auto hi = half ? __builtin_amdgcn_permlane32_swap(xh, yh, false, false) : __builtin_amdgcn_permlane16_swap(xh, yh, false, false);
-  return __longlong_as_double(static_cast<long long>((static_cast<uint64_t>(hi[0]) << 32) | lo[0])) +
-         __longlong_as_double(static_cast<long long>((static_cast<uint64_t>(hi[1]) << 32) | lo[1]));
-}
-__device__ __forceinline__ double wave_sum4(double v0, double v1, double v2, double v3) {
-  return row16_sum(swap_add(swap_add(v0, v2, true), swap_add(v1, v3, true), false));
-}
-
 // Workgroup barrier that orders LDS accesses only: global loads and stores stay in flight.
 __device__ __forceinline__ void lds_barrier() {
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
@@ -47,8 +33,26 @@ __device__ __forceinline__ void lds_barrier() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
-constexpr int kRowsMaxWaves = 16;
-static size_t rows_lds_bytes(int d, int rows) { return static_cast<size_t>(rows) * (d * 2 + 16) + 3 * ((rows + 3) / 4 * 4) * kRowsMaxWaves * sizeof(double); }
+// LDS: R rows, then per row what the waves hand to the wave that adds it up: their lanes' {sum x, sum x^2}; then, in
+// their place, {mean, 1/std}, and behind that the lanes' de-quantized row sums.  (Not a byte more: two workgroups with
+// four rows of 5120 fill a compute unit's 160 KiB.)
+constexpr int kRowsMaxLds = 160 * 1024;
+struct RowsLds {
+  int chunk_waves;                   // waves that hold input chunks
+  int part, part_row;                // byte offset and bytes per row of the parts
+  int bytes;
+};
+template <bool LN>
+__host__ __device__ inline RowsLds rows_lds_layout(int d, int threads, int rows) {
+  RowsLds l;
+  const int nw = threads / kWave, in_chunks = (d / 8 + kWave - 1) / kWave;
+  l.chunk_waves = in_chunks < nw ? in_chunks : nw;
+  const int stats = LN ? l.chunk_waves * kWave * 16 : 0, row_sums = (nw + (LN ? 1 : 0)) * kWave * 8;
+  l.part = rows * d * 2;
+  l.part_row = stats > row_sums ? stats : row_sums;
+  l.bytes = l.part + rows * l.part_row;
+  return l;
+}
 
 template <int BITS, int NUNIT, int NCH, int R, bool LN>
 __global__ void __launch_bounds__(1024) ln_rows_kernel(LnQuantArgs a, LnRowsTab tab) {
@@ -56,16 +60,16 @@ __global__ void __launch_bounds__(1024) ln_rows_kernel(LnQuantArgs a, LnRowsTab 
   constexpr int ND = UC / 4;
   constexpr float kUMax = static_cast<float>((1 << BITS) - 1);
   constexpr int kQMin = -(1 << (BITS - 1));
-  constexpr int RG = (R + 3) / 4;                              // rows are summed four at a time, one per 16 lanes
-  constexpr int RP = RG * 4;
 
-  extern __shared__ __align__(16) unsigned char smem[];        // R row buffers, then the sums
+  extern __shared__ __align__(16) unsigned char smem[];
   const int tid = threadIdx.x, lane = tid & (kWave - 1);
   const int wid = __builtin_amdgcn_readfirstlane(tid >> 6), nw = static_cast<int>(blockDim.x) >> 6;
   const int TU = static_cast<int>(blockDim.x);
-  const int rowbuf_bytes = a.d * 2 + 16;                       // (a spare slot for surplus lanes)
-  // {sum x, sum x^2, de-quantized row sum} of every row and wave
-  auto sums = reinterpret_cast<double(*)[RP][kRowsMaxWaves]>(smem + R * rowbuf_bytes);
+  const RowsLds lds = rows_lds_layout<LN>(a.d, TU, R);
+  const int nwc = lds.chunk_waves;
+  // this lane's parts of row r, wave by wave
+  auto stats_parts = [&](int r) { return reinterpret_cast<double2*>(smem + lds.part + r * lds.part_row) + lane; };
+  auto sum_parts = [&](int r) { return reinterpret_cast<double*>(smem + lds.part + r * lds.part_row) + (LN ? kWave : 0) + lane; };
   const int64_t row0 = static_cast<int64_t>(blockIdx.x) * R;
 
   // ---- every load, rows first: indices are clamped, nothing sits under a lane-dependent branch ------------
@@ -94,41 +98,53 @@ __global__ void __launch_bounds__(1024) ln_rows_kernel(LnQuantArgs a, LnRowsTab 
     }
   }
 
-  // ---- rows to LDS, exact fp64 sums ---------------------------------------------------------------------
-  double s1[RP], s2[RP];
+  // ---- rows to LDS, fp64 sums ---------------------------------------------------------------------------
 #pragma unroll
-  for (int r = 0; r < RP; ++r) s1[r] = s2[r] = 0.0;
-#pragma unroll
-  for (int r = 0; r < R; ++r)
+  for (int r = 0; r < R; ++r) {
+    double s1 = 0.0, s2 = 0.0;
 #pragma unroll
     for (int c = 0; c < NCH; ++c) {
       const int idx = tid + c * TU;
       const bool ok = idx < a.chunks;
-      *reinterpret_cast<u4v*>(smem + r * rowbuf_bytes + (ok ? idx * 16 : a.d * 2)) = x[r][c];
+      if (ok) *reinterpret_cast<u4v*>(smem + r * a.d * 2 + idx * 16) = x[r][c];
       if (LN) {
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
           const uint32_t w = ok ? x[r][c][k] : 0u;
           const double lo = static_cast<double>(bf16_lo(w)), hi = static_cast<double>(bf16_hi(w));
-          s1[r] += lo;
-          s2[r] = fma(lo, lo, s2[r]);
-          s1[r] += hi;
-          s2[r] = fma(hi, hi, s2[r]);
+          s1 += lo;
+          s2 = fma(lo, lo, s2);
+          s1 += hi;
+          s2 = fma(hi, hi, s2);
         }
       }
     }
+    if (LN && wid < nwc) stats_parts(r)[wid * kWave] = make_double2(s1, s2);
+  }
   if (LN) {
+    lds_barrier();                                             // rows and parts are in LDS
+    if (wid < R) {                                             // wave r adds row r up; there are at least R
+      __builtin_amdgcn_s_setprio(3);                           // (the other waves wait for it at the next barrier)
+      double2* part = stats_parts(wid);
+      double t1 = 0.0, t2 = 0.0;
+      for (int j = 0; j < nwc; j += 4) {                       // four reads in flight; surplus ones re-read wave 0
+        double2 v[4];
 #pragma unroll
-    for (int g = 0; g < RP; g += 4) {
-      const double w1 = wave_sum4(s1[g], s1[g + 1], s1[g + 2], s1[g + 3]), w2 = wave_sum4(s2[g], s2[g + 1], s2[g + 2], s2[g + 3]);
-      if ((lane & 15) == 0) {
-        sums[0][g + (lane >> 4)][wid] = w1;
-        sums[1][g + (lane >> 4)][wid] = w2;
+        for (int k = 0; k < 4; ++k) v[k] = part[(j + k < nwc ? j + k : 0) * kWave];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          t1 += j + k < nwc ? v[k].x : 0.0;
+          t2 += j + k < nwc ? v[k].y : 0.0;
+        }
       }
+      float mu, rstd;
+      row_stats(wave_sum(t1), wave_sum(t2), a.d, a.eps, &mu, &rstd);
+      if (lane == 0) *reinterpret_cast<float2*>(part) = make_float2(mu, rstd);
+      __builtin_amdgcn_s_setprio(0);
     }
   }
 
-  // ---- constants of this thread's units (while the sums travel) -------------------------------------------
+  // ---- constants of this thread's units (while the rows are added up) -------------------------------------------
   uint32_t src[NUNIT][UC];           // LDS byte offsets of the source channels inside a row buffer
   uint32_t keep[NUNIT][ND], fill[NUNIT][ND];
   float inv_s[NUNIT], round_back[NUNIT], code_floor[NUNIT];
@@ -178,31 +194,21 @@ __global__ void __launch_bounds__(1024) ln_rows_kernel(LnQuantArgs a, LnRowsTab 
     usum_fix[n] = UC * kQMin - n_real * z;
   }
 
-  lds_barrier();                                               // rows and sums are in LDS
-  float mu[RG], rstd[RG];                                      // lanes 16 k .. 16 k + 15: of row k of the four
-#pragma unroll
-  for (int g = 0; g < RG; ++g) {
-    mu[g] = 0.0f;
-    rstd[g] = 1.0f;
-    if (LN) {
-      const int w = lane & 15, r = g * 4 + (lane >> 4);
-      const double v1 = sums[0][r][w], v2 = sums[1][r][w];
-      row_stats(row16_sum(w < nw ? v1 : 0.0), row16_sum(w < nw ? v2 : 0.0), a.d, a.eps, &mu[g], &rstd[g]);
-    }
-  }
+  lds_barrier();                                               // {mean, 1/std} (without LayerNorm: the rows) are in LDS
 
   // ---- gather in cluster order, normalize, quantize, pack ----------------------------------------------
-  double rt[RP];
-#pragma unroll
-  for (int r = 0; r < RP; ++r) rt[r] = 0.0;
+  double rt[R];
 #pragma unroll
   for (int r = 0; r < R; ++r) {
+    rt[r] = 0.0;
     const bool row_ok = row0 + r < a.M;
-    // (by the lanes' permutation, into vector registers: an operand from a scalar register halves the rate of the
-    // additions and products below)
-    const float mu_r = __builtin_bit_cast(float, __builtin_amdgcn_ds_bpermute(64 * (r % 4), __builtin_bit_cast(int, mu[r / 4])));
-    const float rstd_r = __builtin_bit_cast(float, __builtin_amdgcn_ds_bpermute(64 * (r % 4), __builtin_bit_cast(int, rstd[r / 4])));
-    const unsigned char* rowbuf = smem + r * rowbuf_bytes;
+    float mu_r = 0.0f, rstd_r = 1.0f;
+    if (LN) {
+      const float2 ms = *reinterpret_cast<const float2*>(smem + lds.part + r * lds.part_row);
+      mu_r = ms.x;
+      rstd_r = ms.y;
+    }
+    const unsigned char* rowbuf = smem + r * a.d * 2;
     uint8_t* out_row = a.codes + (row0 + r) * a.row_bytes;
 #pragma unroll
     for (int n = 0; n < NUNIT; ++n) {
@@ -229,32 +235,52 @@ __global__ void __launch_bounds__(1024) ln_rows_kernel(LnQuantArgs a, LnRowsTab 
   }
   if (a.rowterm == nullptr) return;
 #pragma unroll
-  for (int g = 0; g < RP; g += 4) {
-    const double w3 = wave_sum4(rt[g], rt[g + 1], rt[g + 2], rt[g + 3]);
-    if ((lane & 15) == 0) sums[2][g + (lane >> 4)][wid] = w3;
-  }
+  for (int r = 0; r < R; ++r) sum_parts(r)[wid * kWave] = rt[r];
   lds_barrier();
-  if (wid < RG) {
-    const int r = wid * 4 + (lane >> 4);
-    const double v3 = sums[2][r][lane & 15];
-    const double total = row16_sum((lane & 15) < nw ? v3 : 0.0);
-    if ((lane & 15) == 0 && r < R && row0 + r < a.M) a.rowterm[row0 + r] = static_cast<float>(total);
+  if (wid < R) {
+    const double* part = sum_parts(wid);
+    double t3 = 0.0;
+    for (int j = 0; j < nw; j += 4) {
+      double v[4];
+#pragma unroll
+      for (int k = 0; k < 4; ++k) v[k] = part[(j + k < nw ? j + k : 0) * kWave];
+#pragma unroll
+      for (int k = 0; k < 4; ++k) t3 += j + k < nw ? v[k] : 0.0;
+    }
+    const double total = wave_sum(t3);
+    if (lane == 0 && row0 + wid < a.M) a.rowterm[row0 + wid] = static_cast<float>(total);
   }
 }
 
 template <int BITS, int NUNIT, int NCH, int R, bool LN>
-static int32_t launch_rows_kernel(const LnQuantArgs& a, const LnRowsTab& tab, int threads, hipStream_t st) {
-  auto kern = ln_rows_kernel<BITS, NUNIT, NCH, R, LN>;
-  const size_t shmem = rows_lds_bytes(a.d, R);
+static int32_t raise_rows_limit(int d, int threads, hipStream_t st) {
   static LdsGrant lds_granted;
-  if (int32_t s = ensure_dynamic_lds(reinterpret_cast<const void*>(kern), shmem, &lds_granted, st)) return s;
-  hipLaunchKernelGGL(kern, dim3(static_cast<unsigned>((a.M + R - 1) / R)), dim3(threads), shmem, st, a, tab);
+  return ensure_dynamic_lds(reinterpret_cast<const void*>(ln_rows_kernel<BITS, NUNIT, NCH, R, LN>),
+                            rows_lds_layout<LN>(d, threads, R).bytes, &lds_granted, st);
+}
+
+template <int BITS, int NUNIT, int NCH, int R, bool LN>
+static int32_t launch_rows_kernel(const LnQuantArgs& a, const LnRowsTab& tab, int threads, hipStream_t st) {
+  if (int32_t s = raise_rows_limit<BITS, NUNIT, NCH, R, LN>(a.d, threads, st)) return s;
+  hipLaunchKernelGGL((ln_rows_kernel<BITS, NUNIT, NCH, R, LN>), dim3(static_cast<unsigned>((a.M + R - 1) / R)), dim3(threads),
+                     rows_lds_layout<LN>(a.d, threads, R).bytes, st, a, tab);
   RPTQ_HIP(hipGetLastError());
   return RPTQ_OK;
 }
 
 template <int BITS, int NUNIT, int NCH, bool LN>
 static int32_t launch_rows_count(const LnQuantArgs& a, const LnRowsTab& tab, int rows, int threads, hipStream_t st) {
+  // (four of the widest rows do not fit)
+  if (rows == 4 && rows_lds_layout<LN>(a.d, threads, 4).bytes > kRowsMaxLds) rows = 2;
+  if (rows < 4 && rows_lds_layout<LN>(a.d, threads, 4).bytes <= kRowsMaxLds) {
+    // (a call of few rows stands for a recorded call of more: their limits are raised with it)
+    const int32_t s = raise_rows_limit<BITS, NUNIT, NCH, 4, LN>(a.d, threads, st);
+    if (s && s != RPTQ_ERR_CAPTURE) return s;
+  }
+  if (rows < 2) {
+    const int32_t s = raise_rows_limit<BITS, NUNIT, NCH, 2, LN>(a.d, threads, st);
+    if (s && s != RPTQ_ERR_CAPTURE) return s;
+  }
   if (rows == 4) return launch_rows_kernel<BITS, NUNIT, NCH, 4, LN>(a, tab, threads, st);
   if (rows == 2) return launch_rows_kernel<BITS, NUNIT, NCH, 2, LN>(a, tab, threads, st);
   return launch_rows_kernel<BITS, NUNIT, NCH, 1, LN>(a, tab, threads, st);
@@ -270,20 +296,30 @@ static int32_t launch_rows_cfg(const LnQuantArgs& a, const LnRowsTab& tab, int n
 
 // Which calls come here.  R: one workgroup per compute unit as long as there are rows, up to four each (more rows share
 // the per-position constants, 12 bytes a code against the row's 2; eight measured no better).  Beyond that the pipelined
-// kernel catches up, the sooner the wider the row.  us, pipelined | this kernel, LayerNorm rows:
-//      1 x  2048  4.9 |  3.5      333 x 4072 (3 bits)  8.8 |  6.1     2048 x 2048   9.8 |  7.4     32768 x  768  29.0 | 23.5
-//    128 x   768  4.4 |  3.2      512 x 5120          10.3 |  5.7     2048 x 5120  16.3 | 11.2     16384 x 2048  33.4 | 30.9
-//     32 x  5120  7.1 |  4.8     1024 x 5120          12.2 |  7.3     4096 x 5120  23.9 | 20.4      8192 x 4096  36.4 | 35.0
-//     16 x 12288 10.3 |  7.5     1024 x 12288 (3)     17.2 | 13.9     8192 x 5120  38.7 | 37.7 (3 bits 38.9 | 40.3)
-//   and not:  16384 x 4096  58.3 | 66.3    4096 x 6000  26.5 | 30.6    2048 x 8192 (8 bits)  21.0 | 21.7    2048 x 12288  26.1 | 28.8
-// Without LayerNorm alike (16 x 12288 6.8 | 5.2, 2048 x 5120 10.9 | 7.6, 4096 x 5120 15.6 | 14.1, 8192 x 5120 23.6 | 23.8).
+// kernel catches up, the sooner the wider the row and the fewer waves hold it (a row's parts take 16 bytes of LDS per thread,
+// so fewer rows are resident; at 3 bits a row has half the waves).  us in a recorded graph, pipelined | this kernel,
+// 4 bits (or as stated):
+//                       LayerNorm       without                            LayerNorm       without
+//     1 x  2048          4.4 |  2.9     3.0 |  2.2      2048 x  768        6.1 |  4.5     4.3 |  3.3
+//   128 x   768 (8)      3.8 |  3.0     2.8 |  2.5      2048 x  768 (3)    6.7 |  5.5     4.1 |  3.8
+//    32 x  5120          6.3 |  4.0     4.5 |  3.2      8192 x  768       11.2 |  9.2     7.2 |  6.2
+//    16 x 12288          9.1 |  6.1     7.6 |  4.5     16384 x 2048       33.0 | 30.0    19.1 | 19.0
+//   333 x  4072 (3)      8.0 |  5.9     5.4 |  4.5      8192 x 4072       32.8 | 32.2    22.1 | 19.2
+//   512 x  5120          8.6 |  5.4     6.6 |  3.9      2048 x 5120       14.0 | 10.4     9.9 |  7.3
+//  1024 x  5120 (3)     10.8 |  8.3     7.5 |  6.0      4096 x 5120       21.1 | 19.2    14.5 | 14.5
+//  1024 x  8192 (8)     13.3 | 11.1    13.8 |  8.5      1024 x 12288 (3)  16.5 | 13.1    11.1 |  9.3
+//   and not (back to back):    8192 x  768 (3) 11.4 | 11.8    32768 x 1024  33.9 | 36.2    16384 x 2048 (3) 33.9 | 35.4
+//                              4096 x 4072 (3) 21.9 | 25.8     6144 x 4072 (8) 27.0 | 29.3     4096 x 5120 (3) 24.1 | 29.2
 int32_t launch_ln_rows(const LnQuantArgs& a, const ClusterGeom& geom, const QuantTab& qt, int bits, int nunit, int nch,
                        int threads, int cus, hipStream_t st, bool* served) {
   *served = false;
   if (nch > 2 || nunit > 2 || (bits == 3 && nunit > 1)) return RPTQ_OK;
-  const int most = a.d <= 2048 ? 128 : (a.d <= 4096 ? 32 : (a.d <= 5120 ? 16 : 4));     // rows per compute unit
+  const int most = bits == 3 ? (a.d <= 3072 ? 16 : (a.d <= 5120 ? 8 : 4))                                 // rows per compute unit
+                             : (a.d <= 1024 ? 32 : (a.d <= 2048 ? 64 : (a.d <= (bits == 4 ? 4096 : 3072) ? 32 : (a.d <= 5120 ? 16 : 4))));
   if (a.M > static_cast<int64_t>(cus) * most) return RPTQ_OK;
-  const int rows = a.M <= cus ? 1 : (a.M <= 2 * static_cast<int64_t>(cus) ? 2 : 4);
+  // (a wave adds one row up, so there are no more rows than waves)
+  const int waves = threads / kWave;
+  const int rows = a.M <= cus || waves == 1 ? 1 : (a.M <= 2 * static_cast<int64_t>(cus) || waves < 4 ? 2 : 4);
   LnRowsTab tab;
   for (int i = 0; i < RPTQ_MAX_CLUSTERS; ++i) {
     tab.pad_off[i] = i < geom.g ? geom.pad_off[i] : INT32_MAX;
@@ -296,7 +332,7 @@ int32_t launch_ln_rows(const LnQuantArgs& a, const ClusterGeom& geom, const Quan
   if (bits == 3) s = launch_rows_cfg<3, 1>(a, tab, nch, rows, threads, st);
   else if (bits == 4) s = nunit == 1 ? launch_rows_cfg<4, 1>(a, tab, nch, rows, threads, st) : launch_rows_cfg<4, 2>(a, tab, nch, rows, threads, st);
   else s = nunit == 1 ? launch_rows_cfg<8, 1>(a, tab, nch, rows, threads, st) : launch_rows_cfg<8, 2>(a, tab, nch, rows, threads, st);
-  // (four wide rows need a raised LDS limit; while a graph is recorded it cannot be raised, and the other kernel serves)
+  // (several wide rows need a raised LDS limit; while a graph is recorded it cannot be raised, and the other kernel serves)
   if (s == RPTQ_ERR_CAPTURE) return RPTQ_OK;
   *served = s == RPTQ_OK;
   return s;
