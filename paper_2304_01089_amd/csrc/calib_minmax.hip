@@ -9,10 +9,10 @@
 // on an order-preserving integer image of the floats, so the result does not depend on order.
 //
 // What bounds it is the global atomics, 2d per workgroup on the same 2d words, against the depth of one
-// group's row loop: a batch of 128 rows x 2048 channels in 128 one-row workgroups took 22.6 us (and each of 16
-// batches its own launch, 362 us); all 2048 rows in one launch take 15 us with 2 rows per group (128
-// workgroups), 20 us with 4, 31 us with 8.
+// group's row loop: few rows want few workgroups, many rows the whole chip (the rule and its table are in the launcher).
 #include <hip/hip_runtime.h>
+
+#include <cmath>
 
 #include "device_common.h"
 #include "rptq_internal.h"
@@ -20,7 +20,7 @@
 namespace rptq {
 
 constexpr int kCalBatches = 64;           // batches one launch takes (by value)
-constexpr int kCalRowsPerGroup = 2;       // rows a thread group walks (more of them beyond 512 workgroups)
+constexpr int kCalRowsPerGroup = 2;       // rows a thread group walks at least
 
 struct CalBatches {
   int32_t n;
@@ -207,10 +207,30 @@ int32_t launch_channel_minmax(const void* const* x_batches, const int64_t* rows,
     }
     if (total == 0) continue;
     const int64_t per_wg = static_cast<int64_t>(groups) * kCalRowsPerGroup;
-    // What a workgroup costs is its 2 d atomic updates at the end, which all go to the same words: few workgroups that
-    // walk more rows.  us for 16 batches of 128 rows with at most 512 | 128 | 64 workgroups: d = 5120 35.5 | 27.3 | 41.2,
-    // 8000 47.5 | 40.0 | 58.6; rows that fill a workgroup: 12288 386 | 140 | 129, and 4 batches of it 211 | 114 | 75.
-    const int64_t most = groups > 1 ? 128 : 64;
+    // Time of W workgroups: c + a d W + p passes / W (a: a workgroup's 2 d atomic updates at the end, all on the same words;
+    // a pass: one row of every group), so W = sqrt(p / a * passes / d), between 64 and one workgroup per compute unit; where a
+    // pass costs little (no LayerNorm) and there are more than twenty for every one of two per unit, two.  p / a was taken
+    // from this table, us by the largest number of workgroups; * is what the rule takes (or the nearest to it).  Several
+    // groups per workgroup:
+    //   LayerNorm   d = 2048      64    128    256    512     d = 8000      64    128    192    256    512
+    //     2048 rows             21.6  17.3*  17.3   17.3                  59.1   41.4  35.3*   39.5   46.6
+    //     8192                  55.3  34.5   26.8*  32.2                 202.2  112.0   83.3  76.0*   84.2
+    //   131072                 833.1 427.3  229.4* 229.6                3358.5 1699.5 1143.4 871.0*  881.3
+    //   none        d = 5120                                d = 8000
+    //     2048                  23.3  19.9*  22.0   26.9                  32.0  27.6*   27.9   32.1   43.8
+    //    32768                 238.1 132.1   83.4   75.4*                353.7  194.5  138.8  118.5  113.1*
+    // One group (its updates are not in order of address):
+    //   LayerNorm   d = 12288     64    128    192    256    512     none     64     128    192    256    512
+    //      512 rows            77.2*  121.0  168.1  220.6  221.5            62.4*  107.3  153.9  203.9  203.9
+    //     2048                132.1*  148.7  185.3  235.4  377.6            80.6*  117.4  160.2  205.5  368.9
+    //     8192                 345.4  254.8 255.8*  289.2  423.4            165.9 156.4*  191.1  233.5  376.6
+    //    32768                1356.6  752.3  582.7 514.8*  640.6            576.6  354.6  316.1 334.1*  443.7
+    //   131072                5349.7 2718.3 1897.3 1504.6* 1598.9          2197.5 1148.5  843.9 730.6*  761.8
+    constexpr int64_t kUnits = 256;                          // compute units
+    const double passes = static_cast<double>(total) / groups;
+    const double best = std::sqrt((groups > 1 ? 180e3 : 21.5e3) * (gamma ? 2.0 : 1.0) * passes / d);
+    const int64_t most = !gamma && best > 2 * kUnits && passes > 20.0 * 2 * kUnits
+                             ? 2 * kUnits : std::min<int64_t>(std::max<int64_t>(static_cast<int64_t>(best), 64), kUnits);
     const dim3 grid(static_cast<unsigned>(std::min<int64_t>((total + per_wg - 1) / per_wg, most))), block(tpr * groups);
     auto go = [&](auto kern) { hipLaunchKernelGGL(kern, grid, block, shmem, st, cb, d, tpr, gamma, beta, eps, relu, keys); };
     if (gamma) {

@@ -1,6 +1,7 @@
 """Per-channel minimum / maximum over calibration batches against the oracle, bit for bit, at the sizes where the
 kernel's split can go wrong: one and several rows per workgroup, ragged and empty batches, more batches than one
-launch takes, one to four chunks per thread, the last width with several rows per workgroup."""
+launch takes, more rows than the workgroups of a launch take in one pass, one to four chunks per thread, the last width
+with several rows per workgroup."""
 import numpy as np
 import pytest
 
@@ -19,6 +20,7 @@ def dev_bf16(x):
 @pytest.mark.parametrize("ln,relu", [(True, False), (False, False), (False, True)])
 @pytest.mark.parametrize("d,rows", [
     (8, [1]), (520, [3, 0, 70]), (1032, [2] * 67), (2056, [129, 5]), (8064, [17]), (8072, [3, 2]), (16392, [5]),
+    (8, [8200, 1, 9000]), (8064, [500, 0, 300]), (8072, [301]), (16392, [150, 1, 120]),       # several passes per workgroup
 ])
 def test_channel_minmax_bit_exact(d, rows, ln, relu):
     import paper_2304_01089_amd as rp
