@@ -713,6 +713,35 @@ static int32_t launch_cfg(const GemmArgs& a, const GemmTab& tab, const GemmQuant
   return RPTQ_OK;
 }
 
+// The 32 x 128 tile beyond 32 tokens.  With larger tiles part of the chip idles and a wave has no other to run beside; with
+// this one each weight is expanded, and fetched from L2, for 32 tokens instead of 64.  It is always ahead up to one tile per
+// compute unit (256).  From there to three, what counts is the weights' way: an XCD keeps columns to itself, so that its L2
+// serves all their row tiles, where the number of tiles divides by 8, else every row tile may fetch them again; the fewer row
+// tiles and the longer K, the more of the work is weights; and 64 x 128 tiles lose most where they just miss one round.
+// us with weights from memory, larger tiles | 32 x 128, 4 bits, by rows x columns (tiles); * taken:
+//   Y           K = 12288                        K = 5120                         K = 2048
+//     128 x  8192 (256)  38.2 | 33.2 *            96 x  8192 (192)  20.5 | 16.7 *    96 x  8192 (192)  11.1 |  8.6 *
+//      64 x 28672 (448)  43.3 | 45.0              64 x 36864 (576)  30.3 | 32.5      64 x 24576 (384)  12.5 | 11.0 *
+//     128 x 16384 (512)  40.4 | 41.1 *           128 x 20480 (640)  26.5 | 27.0 *    64 x 49152 (768)  15.8 | 17.2
+//     256 x 12288 (768)  49.4 | 52.1             384 x  8192 (768)  26.8 | 27.1 *   256 x 11264 (704)  13.6 | 14.6
+//      96 x 20480 (480)  51.0 | 42.0 *           192 x 13568 (636)  26.6 | 34.4     192 x 10880 (510)  11.9 | 13.8
+//     192 x 13568 (636)  50.2 | 72.9             600 x  3328 (494)  24.5 | 19.0 *   640 x  4864 (760)  14.4 | 13.1 *
+//   next site's codes, 128 x 24576 (768) 58.8 | 61.9, 32.3 | 32.0 *, 19.8 | 18.5 *; a pair per cluster 60.8 | 64.0, 35.3 | 35.3 *,
+//   20.6 | 19.0 *
+static bool few_small_tiles(const GemmArgs& a, bool plain_y) {
+  const int64_t rows = (a.M + 31) / 32, cols = (a.N + 127) / 128, tiles = rows * cols;
+  if (tiles <= 256 || rows >= 16) return tiles <= 768;
+  const bool short_k = a.slices <= 192;
+  if (tiles % 8 != 0) {
+    const bool second_round = (rows + 1) / 2 * cols > 256;               // of 64 x 128 tiles
+    if (rows >= 10) return tiles <= (second_round ? 512 : 384);
+    return short_k && tiles <= (second_round ? 464 : 288);
+  }
+  if (rows < 3) return tiles <= (short_k ? 512 : 288);
+  if (rows < 10) return tiles <= (!short_k ? 512 : (plain_y ? 640 : 768));
+  return tiles <= (short_k ? 768 : 704);
+}
+
 template <int BITS, bool PARTIALS, int OUT, bool CWISE = false>
 static int32_t launch_shape(const GemmArgs& a, const GemmTab& tab, const GemmQuantOut& qo, float* q_rowterm, hipStream_t st) {
   // Every call of more than 32 rows raises the limit of the 64 x 256 tile, whichever kernel serves it: a program that ran
@@ -726,16 +755,7 @@ static int32_t launch_shape(const GemmArgs& a, const GemmTab& tab, const GemmQua
     if (int32_t s = launch_small_gemm(a, tab, BITS, OUT, st, &served)) return s;
     if (served) return RPTQ_OK;
   }
-  // 32 x 128 tile: decoding, and products whose tiles of that shape do not go round more than three times per compute unit:
-  // with larger ones part of the chip idles and a wave has no other to run beside.  Each weight is expanded for 32 tokens
-  // instead of 64, which is what the larger tiles are ahead by from then on.  us for the rule below | 32 x 128 by the number
-  // of 32 x 128 tiles, g = 32 (* 16):
-  //   Y, K = 5120          280: 21.4 | 18.6   640: 26.9 | 24.0   768: 27.1 | 25.1   896: 27.9 | 30.3   1024: 29.0 | 31.8
-  //   Y, K = 12288         512: 39.6 | 34.3   640: 49.2 | 43.4   768: 49.9 | 46.5   896: 52.0 | 56.8   1024: 54.6 | 60.6
-  //   Y, K = 2048*         512: 11.9 | 10.8   640: 14.5 | 13.0   768: 14.6 | 13.1   896: 14.8 | 15.7   1024: 15.0 | 16.1
-  //   next site's codes    576: 31.5 | 28.3   576*: 18.5 | 16.9   832: 31.8 | 34.2   884*: 20.8 | 23.1
-  //   a pair per cluster   320: 27.6 | 23.3   512: 27.8 | 23.6   768: 36.3 | 32.8   1024: 37.9 | 39.1
-  if (a.M <= 32 || (!PARTIALS && (a.M + 31) / 32 * ((a.N + 127) / 128) <= 768))
+  if (a.M <= 32 || (!PARTIALS && few_small_tiles(a, OUT < 2 && !CWISE)))
     return launch_cfg<BITS, 1, 4, 1, 1, PARTIALS, OUT, CWISE>(a, tab, qo, q_rowterm, st);
   // 64 x 256 tile; every wave covers all 64 tokens and 64 output channels: each expanded
   // weight fragment feeds two MFMAs and no two waves expand the same weights.  Two such workgroups fill a compute unit,

@@ -1,5 +1,5 @@
-"""Both sides of the rule that gives a product 32 x 128 tiles (up to 768 of them): a token's outputs are the same, bit for
-bit, whichever tile its call runs on.  (Each kernel is checked against the oracle elsewhere.)"""
+"""Both sides of the rule that gives a product 32 x 128 tiles: a token's outputs are the same, bit for bit, whichever tile
+its call runs on.  (Each kernel is checked against the oracle elsewhere.)"""
 import pytest
 
 pytestmark = pytest.mark.gpu
@@ -7,7 +7,12 @@ torch = pytest.importorskip("torch")
 
 
 @pytest.mark.parametrize("bits", [3, 4, 8])
-@pytest.mark.parametrize("M,N", [(1024, 3064), (2017, 1528), (96, 32760)])
+@pytest.mark.parametrize("M,N", [
+    (1024, 3064), (2017, 1528), (96, 32760),
+    (1024, 3200),                                              # 800 tiles: more than three per compute unit
+    (190, 5376), (190, 5384), (64, 16384), (64, 16392),        # 252 tiles, 258; 256, 258
+    (96, 27136), (96, 27640), (330, 4352), (290, 4992), (352, 8184), (600, 3328), (600, 3336),     # 636, 648; 374, 390; 704; 494, 513
+])
 def test_outputs_do_not_depend_on_the_tile(M, N, bits):
     import paper_2304_01089_amd as rp
     d, g, dev = 328, 9, dict(device="cuda")

@@ -31,3 +31,26 @@ def test_calibration_of_many_rows_uses_the_chip():
     to = torch.empty_like(x)
     copy = shortest(lambda: to.copy_(x))
     assert shortest(lambda: rp.rptq_channel_minmax(list(x), gamma, beta, 1e-5, False, out[0], out[1], ws)) < 2.8 * copy
+
+
+def test_product_of_a_tile_count_that_eight_does_not_divide():
+    """192 tokens, K = 12288, weights from memory: 13568 columns take no longer than 13824 (on 32 x 128 tiles, 636 of them,
+    every XCD fetches every weight: 73 us against 53)."""
+    import numpy as np
+    import paper_2304_01089_amd as rp
+    M, K, g, bits, dev = 192, 12288, 32, 4, dict(device="cuda")
+    off = (np.arange(g + 1) * (K // g)).astype(np.int32)
+    sx = np.full(g, 0.01, np.float32)
+    codes = torch.randint(0, 256, (rp.rptq_codes_bytes(M, K, bits),), dtype=torch.uint8, **dev)
+    time = {}
+    for N in (13568, 13824):
+        W = [torch.randint(0, 256, (rp.rptq_weight_bytes(N, K),), dtype=torch.uint8, **dev) for _ in range(8)]
+        sW, zW, ct, rt = torch.ones(N, **dev), torch.zeros(N, dtype=torch.int32, **dev), torch.zeros(N, **dev), torch.zeros(M, **dev)
+        y = torch.empty(M, N, dtype=torch.bfloat16, **dev)
+
+        def call():
+            for Wq in W:
+                rp.rptq_cluster_gemm(codes, M, bits, Wq, N, off, sx, sW, zW, ct, rt, y)
+        time[N] = shortest(call)
+        del W
+    assert time[13568] < 1.2 * time[13824], time
