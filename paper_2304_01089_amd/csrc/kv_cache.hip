@@ -6,8 +6,8 @@
 // The cache layout is dense (no padding of clusters: the cache is what the method saves
 // memory on), so the quantizer constants are per position, in a device table built once.
 // A reorder index never moves a channel out of its head, so the gather is local: one wave
-// owns a tile of 1024 consecutive channels (whole heads) of a row, stages its 2 KiB through
-// a private piece of LDS and needs no workgroup barrier.
+// owns a tile of 1024 consecutive channels (whole heads) of a row and stages its 2 KiB through
+// a private piece of LDS.  The only workgroup barrier is the one behind the table, which all waves share.
 #include <hip/hip_runtime.h>
 
 #include "device_common.h"
@@ -252,10 +252,12 @@ int32_t launch_kv_quant(const void* x, int64_t T, int32_t d, const KvPos* pos, i
   int cus = 0;
   if (int32_t s = device_compute_units(st, &cus)) return s;
   const int segs = (d + kKvTile - 1) / kKvTile;
-  // about eight workgroups of four waves per compute unit, but at least 32 rows per wave while the
-  // batch allows (a wave's per-lane constants cost as much as eight rows of input); every workgroup
-  // keeps one tile column
-  int64_t row_groups = (static_cast<int64_t>(cus) * 8 + segs - 1) / segs;
+  // Three workgroups of four waves per compute unit, rounded down: one round (25 KiB of LDS leave six resident), and enough
+  // rows in flight.  us by that number 3 | 4 | 6 | 8 (the last a round and a third): 16384 x 12288 at 3 bits 97 | 98 | 106 | 106,
+  // 32768 x 12288 190 | 191 | 217 | 206, 32768 x 5120 at 4 bits 78 | 81 | 80 | 80, 65536 x 5120 153 | 159 | 195 | 173, 65536 x 2048
+  // 64 | 66 | 65 | 65.  But at least 32 rows per wave while that leaves two workgroups per compute unit (a workgroup reads
+  // 16 KiB of table, as much as eight rows of its tile).  Every workgroup keeps one tile column.
+  int64_t row_groups = static_cast<int64_t>(cus) * 3 / segs;
   row_groups = std::min<int64_t>(row_groups, std::max<int64_t>((T + 127) / 128, (static_cast<int64_t>(cus) * 2 + segs - 1) / segs));
   row_groups = std::min<int64_t>(std::max<int64_t>(row_groups, 1), (T + 3) / 4);
   const dim3 grid(static_cast<unsigned>(segs * row_groups)), block(256);
@@ -273,8 +275,8 @@ int32_t launch_kv_dequant(const void* codes, int64_t T, int32_t d, const KvPos* 
   int cus = 0;
   if (int32_t s = device_compute_units(st, &cus)) return s;
   const int blocks_per_row = (d / 8 + 255) / 256;
-  // eight workgroups per compute unit, but at least eight rows per thread while that leaves two per
-  // compute unit (a thread's constants are 128 bytes, eight times a row's store)
+  // eight workgroups per compute unit (20 KiB of LDS each: one round), but at least eight rows per thread while that leaves
+  // two per compute unit (a workgroup reads 32 KiB of table, as much as it stores in eight rows)
   int64_t rows_par = (static_cast<int64_t>(cus) * 8 + blocks_per_row - 1) / blocks_per_row;
   rows_par = std::min<int64_t>(rows_par, std::max<int64_t>((T + 7) / 8, (static_cast<int64_t>(cus) * 2 + blocks_per_row - 1) / blocks_per_row));
   rows_par = std::min<int64_t>(std::max<int64_t>(rows_par, 1), T);

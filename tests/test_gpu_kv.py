@@ -48,6 +48,7 @@ CASES = [
     ("a8", 33, 4, 128, 8, 4),
     ("one_row_a3", 1, 16, 64, 3, 3),
     ("whole_tile_heads", 20, 3, 1024, 4, 8),     # a head as wide as a wave tile
+    ("many_rows_a3", 100003, 1, 64, 3, 4),       # more rows than one workgroup per 128 of them
 ]
 
 
