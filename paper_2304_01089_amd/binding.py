@@ -7,6 +7,7 @@ from __future__ import annotations
 
 import ctypes as C
 import os
+import sys
 from typing import Optional, Sequence
 
 import numpy as np
@@ -28,6 +29,7 @@ EXPORTED_SYMBOLS = (
 
 _LIB = None
 _CALLS = None             # the native marshalling module, once a library is loaded and torch is there
+_CALLS_SOUGHT = False
 
 
 class RptqError(RuntimeError):
@@ -53,6 +55,8 @@ def load_library():
     """Loads the built library; raises if it has not been built (no fallback exists)."""
     global _LIB
     if _LIB is not None:
+        if not _CALLS_SOUGHT and "torch" in sys.modules:       # (torch came after the library)
+            _set_up_calls(_LIB)
         return _LIB
     path = library_path()
     if not os.path.exists(path):
@@ -107,15 +111,16 @@ def load_library():
         fn.restype = res
         fn.argtypes = args
     _LIB = lib
-    _set_up_calls(lib)
+    if "torch" in sys.modules:                                 # (a program that calls the host functions only goes without)
+        _set_up_calls(lib)
     return lib
 
 
 def _set_up_calls(lib):
     """Points the native marshalling (csrc/calls.cpp, built beside the library) at the loaded library.  Without it, or
     without torch, the functions below marshal in Python."""
-    global _CALLS
-    _CALLS = None
+    global _CALLS, _CALLS_SOUGHT
+    _CALLS, _CALLS_SOUGHT = None, True
     try:
         import torch
         from . import _calls

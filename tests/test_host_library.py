@@ -4,6 +4,8 @@ codec used by the GPU tests round-trips.  No kernel is launched here."""
 import ctypes
 import os
 import re
+import subprocess
+import sys
 
 import numpy as np
 import pytest
@@ -252,3 +254,27 @@ def test_first_method_entry_points_validate_on_the_host(lib):
     assert lib.rptq_dequant_codes(fake, 4, 4, off, 2, bad, zx, fake, None) == -6           # scale not finite
     assert lib.rptq_dequant_weights(fake, 0, off, 2, fake, fake, fake, None) == -2
     assert lib.rptq_dequant_weights(None, 4, off, 2, fake, fake, fake, None) == -1
+
+
+def test_the_host_functions_do_not_import_torch():
+    """Loading the library and calling what runs on the host leaves torch out; the native marshalling is found on the first
+    call after torch came in."""
+    program = """
+import sys
+import numpy as np
+import paper_2304_01089_amd as rp
+from paper_2304_01089_amd import binding
+rp.load_library()
+assert rp.rptq_padded_k([0, 40, 64]) == 256
+assert "torch" not in sys.modules
+import torch
+t = torch.zeros(4, 32, dtype=torch.bfloat16)
+try:
+    rp.rptq_kv_quant(t, 4, 32, t, 4, t)
+except ValueError:
+    pass
+rp.rptq_padded_k([0, 40, 64])
+assert binding._CALLS is not None
+"""
+    r = subprocess.run([sys.executable, "-c", program], cwd=ROOT, capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr
