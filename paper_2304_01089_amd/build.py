@@ -7,6 +7,7 @@ import subprocess
 import sys
 import sysconfig
 from concurrent.futures import ThreadPoolExecutor
+from typing import Optional
 
 PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
@@ -45,11 +46,20 @@ def _compile(src: str, objdir: str, verbose: bool) -> str:
     return obj
 
 
-def build_calls() -> str:
-    """Compile the CPython module beside the library (host code only)."""
+def build_calls() -> Optional[str]:
+    """Compile the CPython module beside the library (host code only).  Where there is no C++ compiler of the host's, or no
+    header of this Python's, there is no module (None): the binding does the same in Python."""
+    include = sysconfig.get_paths()["include"]
+    lacks = [what for what, there in (("g++", shutil.which("g++")), ("Python.h", os.path.exists(os.path.join(include, "Python.h"))))
+             if not there]
+    if lacks:
+        sys.stderr.write("no native marshalling of calls: %s not found\n" % " and ".join(lacks))
+        if os.path.exists(CALLS):                # (of an older source)
+            os.remove(CALLS)
+        return None
     tmp = CALLS + ".tmp"
     cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-I", os.path.join(ROOT, "include"),
-           "-I", sysconfig.get_paths()["include"], os.path.join(CSRC, "calls.cpp"), "-o", tmp]
+           "-I", include, os.path.join(CSRC, "calls.cpp"), "-o", tmp]
     res = subprocess.run(cmd, capture_output=True, text=True)
     if res.returncode != 0:
         raise RuntimeError("g++ failed for calls.cpp:\n%s\n%s" % (res.stdout, res.stderr))

@@ -278,3 +278,18 @@ assert binding._CALLS is not None
 """
     r = subprocess.run([sys.executable, "-c", program], cwd=ROOT, capture_output=True, text=True)
     assert r.returncode == 0, r.stderr
+
+
+@pytest.mark.parametrize("lacks", ["g++", "Python.h"])
+def test_build_without_what_the_native_marshalling_needs(lacks, tmp_path, monkeypatch, capsys):
+    """hipcc alone builds the library; a module of an older source does not stay."""
+    from paper_2304_01089_amd import build
+    module = tmp_path / "_calls.so"
+    module.write_bytes(b"older")
+    monkeypatch.setattr(build, "CALLS", str(module))
+    if lacks == "g++":
+        monkeypatch.setattr(build.shutil, "which", lambda name: None)
+    else:
+        monkeypatch.setattr(build.sysconfig, "get_paths", lambda: dict(include=str(tmp_path)))
+    assert build.build_calls() is None
+    assert not module.exists() and lacks in capsys.readouterr().err
