@@ -13,7 +13,8 @@ PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 LIB = os.path.join(PKG, "librptq.so")
-CALLS = os.path.join(PKG, "_calls.so")          # the binding's native argument marshalling (csrc/calls.cpp)
+# the binding's native argument marshalling (csrc/calls.cpp); the suffix keeps other interpreters from loading it
+CALLS = os.path.join(PKG, "_calls" + sysconfig.get_config_var("EXT_SUFFIX"))
 SOURCES = ["host.cpp", "api.cpp", "calib_minmax.hip", "fold.hip", "ln_quant.hip", "ln_rows.hip", "gemm.hip", "gemm_small.hip", "kv_cache.hip", "ln_scatter.hip", "method1.hip"]
 
 FLAGS = [
@@ -49,6 +50,9 @@ def _compile(src: str, objdir: str, verbose: bool) -> str:
 def build_calls() -> Optional[str]:
     """Compile the CPython module beside the library (host code only).  Where there is no C++ compiler of the host's, or no
     header of this Python's, there is no module (None): the binding does the same in Python."""
+    untagged = os.path.join(os.path.dirname(CALLS), "_calls.so")
+    if os.path.exists(untagged):                 # (any interpreter would load it)
+        os.remove(untagged)
     include = sysconfig.get_paths()["include"]
     lacks = [what for what, there in (("g++", shutil.which("g++")), ("Python.h", os.path.exists(os.path.join(include, "Python.h"))))
              if not there]

@@ -2,6 +2,7 @@
 host logic (sizes, validation, clustering) agrees with the oracle, and the packed-layout
 codec used by the GPU tests round-trips.  No kernel is launched here."""
 import ctypes
+import importlib.machinery
 import os
 import re
 import subprocess
@@ -284,7 +285,7 @@ assert binding._CALLS is not None
 def test_build_without_what_the_native_marshalling_needs(lacks, tmp_path, monkeypatch, capsys):
     """hipcc alone builds the library; a module of an older source does not stay."""
     from paper_2304_01089_amd import build
-    module = tmp_path / "_calls.so"
+    module = tmp_path / os.path.basename(build.CALLS)
     module.write_bytes(b"older")
     monkeypatch.setattr(build, "CALLS", str(module))
     if lacks == "g++":
@@ -293,3 +294,13 @@ def test_build_without_what_the_native_marshalling_needs(lacks, tmp_path, monkey
         monkeypatch.setattr(build.sysconfig, "get_paths", lambda: dict(include=str(tmp_path)))
     assert build.build_calls() is None
     assert not module.exists() and lacks in capsys.readouterr().err
+
+
+def test_the_native_marshalling_is_of_one_interpreter(tmp_path, monkeypatch):
+    from paper_2304_01089_amd import build
+    name = os.path.basename(build.CALLS)
+    assert name == "_calls" + importlib.machinery.EXTENSION_SUFFIXES[0] and name != "_calls.so"
+    monkeypatch.setattr(build, "CALLS", str(tmp_path / name))
+    (tmp_path / "_calls.so").write_bytes(b"untagged")
+    build.build_calls()
+    assert not (tmp_path / "_calls.so").exists()
