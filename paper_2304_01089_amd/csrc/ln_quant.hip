@@ -418,9 +418,12 @@ __global__ void xsum_kernel(const uint8_t* codes, int64_t M, int32_t row_bytes, 
 // cluster, so a lane adds whole groups into the cluster's integer sum (exact, order-free).
 // Output position of cluster i in a row of g2 floats: (i & 1) * g2/2 + i/2 (the operand order
 // of the 32x32x2 fp32 MFMA that consumes it).
+constexpr int kRowSumPasses = (RPTQ_MAX_CHANNELS + kGroup * RPTQ_MAX_CLUSTERS) / (kGroup * kWave) + 1;
 struct RowSumTab {
   double s[RPTQ_MAX_CLUSTERS];
   double nz[RPTQ_MAX_CLUSTERS];        // n_i * zX_i
+  uint64_t starts[kRowSumPasses];      // bit j of word p: a cluster starts at group 64 p + j
+  int32_t g, groups;
 };
 
 // Sum of a 32-code group's codes, times 2^shift of the operand bytes (4, 5 or 0): the codes expanded as the products
@@ -463,14 +466,15 @@ __device__ __forceinline__ int wave_scan(int v) {
   return v;
 }
 
-// A wave takes a row in passes of 64 groups, one per lane.  The cluster table sits in a register (lane i: cluster i); a
-// pass looks at the few clusters that it meets only, and where a cluster ends or the pass does, the running sum over
-// the lanes goes into the cluster's sum, and out of the next one's: at most two additions per cluster, to different
-// words.  (Searching all clusters for every group, by scalar loads, and adding every group to its cluster's word was
-// 6.5 us for 2048 rows of 5120 and 12.5 for 16 of 12288; this is 4.6 and 5.0.)
+// A wave takes a row in passes of 64 groups, one per lane.  Where the clusters start is a bit mask per pass: a lane's cluster
+// is a count of bits, and where a cluster ends or the pass does, the running sum over the lanes goes into the cluster's
+// sum, and out of the next one's: at most two additions per cluster, to different words.  us, rows x channels at 4 bits, 32
+// clusters, all clusters searched for every group and every group added to its cluster's word | a pass's clusters walked
+// through, from a register | this: 1 x 768 3.0 | 3.5 | 2.2, 8192 x 768 5.7 | 6.7 | 3.3, 2048 x 5120 6.0 | 4.6 | 3.2, 1 x 12288 8.5 | 4.2 |
+// 2.9, 8192 x 12288 21.0 | 11.2 | 10.0.
 template <int BITS>
 __global__ void __launch_bounds__(256) cluster_rowsums_kernel(const uint8_t* codes, int64_t M, int32_t row_bytes,
-                                                              ClusterGeom geom, RowSumTab tab, float* rtc, int32_t g2) {
+                                                              RowSumTab tab, float* rtc, int32_t g2) {
   constexpr int GB = BITS * 4, ND = GB / 4;
   constexpr int kShift = BITS == 8 ? 0 : (BITS == 4 ? 4 : 5);
   __shared__ int32_t acc[4][RPTQ_MAX_CLUSTERS];
@@ -478,9 +482,8 @@ __global__ void __launch_bounds__(256) cluster_rowsums_kernel(const uint8_t* cod
   const int64_t row = static_cast<int64_t>(blockIdx.x) * 4 + wave;
   if (row >= M) return;
   acc[wave][lane] = 0;
-  const int t_off = lane < geom.g ? geom.pad_off[lane] / kGroup : INT32_MAX;      // first group of cluster `lane`
   const double t_s = tab.s[lane], t_nz = tab.nz[lane];
-  const int groups = geom.pad_off[geom.g] / kGroup;
+  const int groups = tab.groups;
   const uint8_t* src = codes + row * row_bytes;
   auto load = [&](int gi, uint32_t (&w)[ND]) {
     const uint32_t* p = reinterpret_cast<const uint32_t*>(src + static_cast<int64_t>(min(gi, groups - 1)) * GB);
@@ -490,18 +493,16 @@ __global__ void __launch_bounds__(256) cluster_rowsums_kernel(const uint8_t* cod
   uint32_t w[ND], nxt[ND];
   load(lane, w);
   wave_lds_fence();
-  for (int g0 = 0; g0 < groups; g0 += kWave) {
+  int started = -1;                                          // clusters that have started before the pass, less one
+  for (int g0 = 0, p = 0; g0 < groups; g0 += kWave, ++p) {
     const int gi = g0 + lane;
     load(gi + kWave, nxt);
     const int sum = wave_scan(gi < groups ? group_sum<BITS>(w) : 0);
-    const int c_first = __builtin_popcountll(__ballot(t_off <= g0)), c_last = __builtin_popcountll(__ballot(t_off < g0 + kWave));
-    int ci = c_first - 1;
-    bool ends = lane == kWave - 1;                           // the lane's group is its cluster's last one of this pass
-    for (int i = c_first; i < c_last; ++i) {
-      const int start = __builtin_amdgcn_readlane(t_off, i);
-      ci += gi >= start ? 1 : 0;
-      ends |= gi == start - 1;
-    }
+    const uint64_t starts = tab.starts[p], next = starts >> 1;                 // next: bit j, a cluster starts behind lane j
+    const uint32_t lo = static_cast<uint32_t>(next), hi = static_cast<uint32_t>(next >> 32);
+    const int ci = started + static_cast<int>(starts & 1) + static_cast<int>(__builtin_amdgcn_mbcnt_hi(hi, __builtin_amdgcn_mbcnt_lo(lo, 0)));
+    const bool ends = lane == kWave - 1 || ((next >> lane) & 1) != 0;            // the cluster's last group of this pass
+    started += __builtin_popcountll(starts);
     if (ends) {
       atomicAdd(&acc[wave][ci], sum);
       if (lane < kWave - 1) atomicAdd(&acc[wave][ci + 1], -sum);
@@ -512,7 +513,7 @@ __global__ void __launch_bounds__(256) cluster_rowsums_kernel(const uint8_t* cod
   wave_lds_fence();
   if (lane < g2) {
     float v = 0.0f;
-    if (lane < geom.g) v = static_cast<float>(t_s * (static_cast<double>(acc[wave][lane] >> kShift) - t_nz));
+    if (lane < tab.g) v = static_cast<float>(t_s * (static_cast<double>(acc[wave][lane] >> kShift) - t_nz));
     rtc[row * g2 + (lane & 1) * (g2 / 2) + (lane >> 1)] = v;
   }
 }
@@ -674,9 +675,12 @@ int32_t launch_ln_quant(const void* x, int64_t M, int32_t d, const float* gamma_
 int32_t launch_cluster_rowsums(const void* codes, int64_t M, const ClusterGeom& geom, int32_t bits, const float* sX,
                                const int32_t* zX, float* rtc, hipStream_t st) {
   if (M == 0) return RPTQ_OK;
-  RowSumTab tab;
+  RowSumTab tab = {};
+  tab.g = geom.g;
+  tab.groups = geom.pad_off[geom.g] / kGroup;
   for (int i = 0; i < RPTQ_MAX_CLUSTERS; ++i) {
     const bool in = i < geom.g;
+    if (in) tab.starts[geom.pad_off[i] / kGroup / kWave] |= uint64_t{1} << (geom.pad_off[i] / kGroup % kWave);
     tab.s[i] = in ? static_cast<double>(sX[i]) : 0.0;
     tab.nz[i] = in ? static_cast<double>(geom.off[i + 1] - geom.off[i]) * static_cast<double>(zX[i]) : 0.0;
   }
@@ -684,9 +688,9 @@ int32_t launch_cluster_rowsums(const void* codes, int64_t M, const ClusterGeom& 
   const uint8_t* c = static_cast<const uint8_t*>(codes);
   const int32_t row_bytes = geom.k_padded * bits / 8;
   const dim3 grid(static_cast<unsigned>((M + 3) / 4)), block(256);
-  if (bits == 3) hipLaunchKernelGGL(cluster_rowsums_kernel<3>, grid, block, 0, st, c, M, row_bytes, geom, tab, rtc, g2);
-  else if (bits == 4) hipLaunchKernelGGL(cluster_rowsums_kernel<4>, grid, block, 0, st, c, M, row_bytes, geom, tab, rtc, g2);
-  else hipLaunchKernelGGL(cluster_rowsums_kernel<8>, grid, block, 0, st, c, M, row_bytes, geom, tab, rtc, g2);
+  if (bits == 3) hipLaunchKernelGGL(cluster_rowsums_kernel<3>, grid, block, 0, st, c, M, row_bytes, tab, rtc, g2);
+  else if (bits == 4) hipLaunchKernelGGL(cluster_rowsums_kernel<4>, grid, block, 0, st, c, M, row_bytes, tab, rtc, g2);
+  else hipLaunchKernelGGL(cluster_rowsums_kernel<8>, grid, block, 0, st, c, M, row_bytes, tab, rtc, g2);
   RPTQ_HIP(hipGetLastError());
   return RPTQ_OK;
 }

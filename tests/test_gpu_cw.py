@@ -225,3 +225,27 @@ def test_ragged_tiles_of_every_width(rp, bits):
         assert (y[M] == 7.0).all()
         got = y[:M].float().cpu().numpy().astype(np.float64)
         assert (np.abs(got - Y) <= tol_of(Y) + (np.abs(Y) * 2.0 ** -7 if dtype == torch.bfloat16 else 0.0)).all()
+
+
+@pytest.mark.parametrize("bits", [3, 4, 8])
+@pytest.mark.parametrize("sizes", [
+    [1], [2048], [2049], [64 * 32 * 3 + 5],                    # one cluster: a pass to the last lane, one group more, several passes
+    [63 * 32, 32, 32], [63 * 32 + 1, 31, 7], [64 * 32, 1],     # a cluster starts at the last lane, and at the next pass's first
+    [65 * 32, 1, 62 * 32, 40], [5] * 32, [1] * 31 + [5000],
+    [4000] + [32] * 30 + [1000], [32768],
+])
+def test_row_sums_at_the_edges_of_a_pass(rp, sizes, bits):
+    """Exact integer sums, one fp64 product, one rounding: bit for bit."""
+    rng = np.random.default_rng(sum(sizes) + len(sizes) + bits)
+    off = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int32)
+    g, M = len(sizes), 6
+    q = rng.integers(-(1 << (bits - 1)), 1 << (bits - 1), (M, off[-1]))
+    q[0], q[1] = -(1 << (bits - 1)), (1 << (bits - 1)) - 1     # (the largest sums)
+    s = np.exp(rng.normal(-2, 1, g)).astype(np.float32)
+    z = rng.integers(-1000, 1000, g).astype(np.int32)
+    out = torch.full((M, 32), 7.0, device="cuda")
+    rp.rptq_cluster_rowsums(dev(packfmt.pack_codes(q, off, bits)), M, bits, off, s, z, out)
+    want = np.zeros((M, 32), np.float32)
+    for i in range(g):
+        want[:, tab_col(i)] = (s[i].astype(np.float64) * (q[:, off[i]:off[i + 1]].sum(axis=1) - sizes[i] * np.float64(z[i]))).astype(np.float32)
+    assert np.array_equal(out.cpu().numpy(), want)
