@@ -310,12 +310,22 @@ static int32_t launch_rows_cfg(const LnQuantArgs& a, const LnRowsTab& tab, int n
 //  1024 x  8192 (8)     13.3 | 11.1    13.8 |  8.5      1024 x 12288 (3)  16.5 | 13.1    11.1 |  9.3
 //   and not (back to back):    8192 x  768 (3) 11.4 | 11.8    32768 x 1024  33.9 | 36.2    16384 x 2048 (3) 33.9 | 35.4
 //                              4096 x 4072 (3) 21.9 | 25.8     6144 x 4072 (8) 27.0 | 29.3     4096 x 5120 (3) 24.1 | 29.2
+// Narrow rows from memory, 4 bits, 8 clusters:
+//                   LayerNorm                                        without
+//             8192       16384       32768               8192        16384       32768       65536
+//     256  10.5 |  8.2  14.7 | 13.7  23.4 | 24.1       6.4 |  6.1   8.4 |  9.4  12.4 | 16.4  20.3 | 28.6
+//     768  13.0 | 10.6  20.7 | 19.1  33.2 | 32.5       8.3 |  7.5  12.9 | 12.4  19.4 | 21.5  35.0 | 38.1
+//    1536  16.9 | 15.2  25.2 | 25.4  42.0 | 45.3      11.4 | 10.6  16.9 | 17.2  27.7 | 30.2  51.2 | 54.4
+//    2048  20.0 | 17.8  31.9 | 31.1  55.8 | 55.6      14.3 | 12.5  23.1 | 19.7  41.3 | 33.5  78.7 | 62.6
 int32_t launch_ln_rows(const LnQuantArgs& a, const ClusterGeom& geom, const QuantTab& qt, int bits, int nunit, int nch,
                        int threads, int cus, hipStream_t st, bool* served) {
   *served = false;
   if (nch > 2 || nunit > 2 || (bits == 3 && nunit > 1)) return RPTQ_OK;
-  const int most = bits == 3 ? (a.d <= 3072 ? 16 : (a.d <= 5120 ? 8 : 4))                                 // rows per compute unit
-                             : (a.d <= 1024 ? 32 : (a.d <= 2048 ? 64 : (a.d <= (bits == 4 ? 4096 : 3072) ? 32 : (a.d <= 5120 ? 16 : 4))));
+  const bool ln = a.gamma_pad != nullptr;
+  int most;                                                  // rows per compute unit
+  if (bits == 3) most = a.d <= 3072 ? 16 : (a.d <= 5120 ? 8 : 4);
+  else if (a.d <= 2048) most = ln ? 64 : (a.d <= 640 ? 32 : (a.d <= 1792 ? 64 : 128));
+  else most = a.d <= (bits == 4 ? 4096 : 3072) ? 32 : (a.d <= 5120 ? 16 : 4);
   if (a.M > static_cast<int64_t>(cus) * most) return RPTQ_OK;
   // (a wave adds one row up, so there are no more rows than waves)
   const int waves = threads / kWave;

@@ -12,11 +12,13 @@ torch = pytest.importorskip("torch")
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 
-def rows_per_unit(d, bits):
+def rows_per_unit(d, bits, ln):
     """The rule: up to so many rows per compute unit."""
     if bits == 3:
         return 16 if d <= 3072 else 8 if d <= 5120 else 4
-    return 32 if d <= 1024 else 64 if d <= 2048 else 32 if d <= (4096 if bits == 4 else 3072) else 16 if d <= 5120 else 4
+    if d <= 2048:
+        return 64 if ln else 32 if d <= 640 else 64 if d <= 1792 else 128
+    return 32 if d <= (4096 if bits == 4 else 3072) else 16 if d <= 5120 else 4
 
 
 def make_call(d, g, bits, M, seed=3, ln=True):
@@ -52,7 +54,7 @@ def make_call(d, g, bits, M, seed=3, ln=True):
 @pytest.mark.parametrize("d,g", [(8, 1), (776, 64), (2048, 16), (2056, 9), (5120, 32), (8184, 32), (12288, 33), (15000, 8)])
 def test_few_rows_equal_many(d, g, bits, ln):
     import paper_2304_01089_amd as rp
-    most = rows_per_unit(d, bits)
+    most = rows_per_unit(d, bits, ln)
     cus = rp.rptq_device_info()["compute_units"]
     many = cus * most + 1
     call = make_call(d, g, bits, many, ln=ln)
@@ -72,7 +74,7 @@ def test_sums_that_show_their_order(d, bits, ln):
     +-2^58 among ordinary values (codes of the ordinary values follow it: scale 2^-58), without it the row sum over two
     outer clusters of scale 2^58.  The same bits still, in both kernels."""
     import paper_2304_01089_amd as rp
-    dev, M, rng = dict(device="cuda"), rp.rptq_device_info()["compute_units"] * rows_per_unit(d, bits) + 1, np.random.default_rng(d + bits)
+    dev, M, rng = dict(device="cuda"), rp.rptq_device_info()["compute_units"] * rows_per_unit(d, bits, ln) + 1, np.random.default_rng(d + bits)
     gen = torch.Generator(device="cuda").manual_seed(d)
     off = np.array([0, 40, d - 40, d], np.int32)
     big = 2.0 ** 58
