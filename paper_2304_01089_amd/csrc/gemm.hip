@@ -338,8 +338,8 @@ __global__ void __launch_bounds__(256, 2) cluster_gemm_kernel(GemmArgs a, GemmTa
 
       const int gs = step * kStepSlices + s + 1;           // slices accumulated so far
       // Cluster ci is complete (uniform branch).  For the large tiles the rescale is placed out of line, so that a slice that
-      // ends no cluster runs straight on: 8192 x 49152 x 12288 4118 -> 4090 us, 4096 x 5120 x 20480 352 -> 347; the 32 x 128
-      // tile, which does less between two branches, is 0.5 % slower with it.
+      // ends no cluster runs straight on: 8192 x 49152 x 12288 4166 -> 4118 us, 4096 x 5120 x 20480 356 -> 350 (four runs of each in
+      // turn), no difference at 64 clusters; the 32 x 128 tile, which does less between two branches, is 0.5 % slower with it.
       if (__builtin_expect(gs == next_end, WM * WN > 1 ? 0 : 1)) {
         if (PARTIALS) {
           const int zx = __builtin_amdgcn_readlane(tab_zx, ci), nn = __builtin_amdgcn_readlane(tab_n, ci);

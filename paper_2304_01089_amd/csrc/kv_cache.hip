@@ -40,7 +40,7 @@ __global__ void __launch_bounds__(256) kv_quant_kernel(const uint4* x, int64_t T
   constexpr float kUMax = static_cast<float>((1 << BITS) - 1);
   // The tile's table records, read by the whole workgroup in order.  (A lane's 16 records are 256 bytes of their own:
   // requested by the lanes that need them, every request touches 64 cache lines, and that was most of the time of few rows:
-  // 16 x 2048 5.6 -> 3.1 us, 1000 x 2048 9.4 -> 4.5, 1000 x 12288 16.4 -> 12.3, 8192 x 12288 46 -> 42.)  16 bytes follow
+  // 16 x 2048 5.6 -> 3.1 us; from memory, 4 bits, 1000 x 2048 10.2 -> 5.3, 1000 x 12288 17.8 -> 10.9, 8192 x 12288 57 -> 51.)  16 bytes follow
   // every lane's records, so that eight lanes read from different banks.
   constexpr int kLaneTab = kKvLaneCodes * 16 + 16;
   __shared__ __align__(16) unsigned char tab[kWave * kLaneTab];
@@ -138,8 +138,8 @@ __global__ void __launch_bounds__(256) kv_quant_kernel(const uint4* x, int64_t T
 // Read-back.  Memory bound (d*bits/8 bytes in, 2d out per row), so the stores decide: a lane expands 8
 // consecutive codes of a row into one 16-byte store, a wave's store is 1 KiB contiguous.  One lane per 32-code group with
 // four 16-byte stores 64 bytes apart took 91 us at 8192 x 12288, 3 bits, this split 68, with non-temporal stores 42 us
-// (5.7 TB/s).  But attention reads the values next, and non-temporal stores send them past the 256 MiB last-level cache:
-// they are used only where the keys and values of a layer together would not stay in it.  us for key and value of one
+// (5.7 TB/s; 39 to 50 inside a pass).  But attention reads the values next, and non-temporal stores send them past the
+// 256 MiB last-level cache: they are used only where the keys and values of a layer together would not stay in it.  us for key and value of one
 // layer, the two read-backs alone and followed by a full read of both, ordinary | non-temporal:
 //    17 MB each   13.8 | 11.8    48 |  50        101 MB   48 | 47   101 | 119
 //    34 MB        23.0 | 19.8    57 |  61        151 MB  110 | 64   211 | 170
@@ -156,9 +156,10 @@ __global__ void __launch_bounds__(256) kv_dequant_kernel(const uint8_t* codes, i
   typedef __bf16 b2 __attribute__((ext_vector_type(2)));
   typedef unsigned u4v __attribute__((ext_vector_type(4)));
   constexpr int ND = (BITS == 3) ? 3 : BITS / 4;       // dwords a lane reads per row
-  // (s, z) of the workgroup's 2048 positions: the table is read in order and changes threads in LDS, as in kv_quant.  (us
-  // for rows x channels, each thread reading its own 128 bytes of table | this: 4096 x 2048 6.9 | 5.9, 1000 x 5120 at 8 bits
-  // 6.0 | 4.8, 2000 x 12288 at 3 bits 14.5 | 11.6, 8192 x 12288 41.6 | 39.3.)  16 bytes follow every thread's 64.
+  // (s, z) of the workgroup's 2048 positions: the table is read in order and changes threads in LDS, as in kv_quant.  (From
+  // memory, us for rows x channels, each thread reading its own 128 bytes of table | this: 4096 x 2048 8.1 | 7.1, 1000 x 2048
+  // at 8 bits 5.2 | 4.4, 1000 x 12288 at 3 bits 10.9 | 9.0, 2048 x 12288 at 8 bits 23.1 | 18.5, 65536 x 768 at 8 bits 31.4 | 33.0.)
+  // 16 bytes follow every thread's 64.
   typedef unsigned u2v __attribute__((ext_vector_type(2)));
   __shared__ __align__(16) unsigned char tab[256 * 80];
   const int u0 = static_cast<int>(blockIdx.x % blocks_per_row) * 256;
