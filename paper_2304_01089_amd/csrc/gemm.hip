@@ -29,8 +29,11 @@ namespace rptq {
 // sX_i sW[o,i] (a table of the tile's columns in LDS), and the zero-point cross term
 // sum_i sW[o,i] zW[o,i] * sX_i (xsum[t,i] - n_i zX_i) is a rank-g update of the fp32 tile, done
 // on the matrix cores (32x32x2 fp32 MFMA) before the output stage.
+// One tile: number `block` of the `total` = tiles_m x tiles_n tiles that cover the columns from n_base on.  `slot0`: what
+// the column tile's number counts from in the quantizing stage's row sums.
 template <int BITS, int WGM, int WGN, int WM, int WN, bool PARTIALS, int OUT, bool CWISE>
-__global__ void __launch_bounds__(256, 2) cluster_gemm_kernel(GemmArgs a, GemmTab tab, GemmQuantOut qo) {
+__device__ __forceinline__ void gemm_tile(const GemmArgs& a, const GemmTab& tab, const GemmQuantOut& qo, int block,
+                                          int tiles_n, int n_base, int slot0) {
   constexpr bool YF32 = OUT == kOutF32;
   constexpr bool QOUT = OUT >= 2;
   constexpr int BM = WGM * WM * 32;
@@ -65,9 +68,9 @@ __global__ void __launch_bounds__(256, 2) cluster_gemm_kernel(GemmArgs a, GemmTa
   const int wm = wave / WGN, wn = wave % WGN;
   // Workgroups are dealt round-robin to the 8 XCDs (each with its own L2): give every XCD a
   // contiguous band of output columns, all row tiles of one column tile back to back.
-  const int tiles_m = a.tiles_m, tiles_n = a.tiles_n;
+  const int tiles_m = a.tiles_m;
   const int total = tiles_m * tiles_n;
-  int lin = blockIdx.x;
+  int lin = block;
   if (total % 8 == 0) lin = (lin & 7) * (total >> 3) + (lin >> 3);
   // The workgroups resident on an XCD at one time (64 with two per compute unit) should share
   // operands in its L2: blocks of grp_m row tiles x grp_n column tiles (16 x 4 tiles: 5 MB + 6.7 MB of
@@ -82,7 +85,7 @@ __global__ void __launch_bounds__(256, 2) cluster_gemm_kernel(GemmArgs a, GemmTa
     tn = GN * group + r % wg;
   }
   const int64_t m0 = static_cast<int64_t>(tm) * BM;
-  const int n0 = tn * BN;
+  const int n0 = n_base + tn * BN;
 
   // ---- global -> register staging ------------------------------------------------------
   uint32_t ra[2][A_PER][A_REGS];                          // two staging sets: loads run ahead of use
@@ -636,9 +639,24 @@ __global__ void __launch_bounds__(256, 2) cluster_gemm_kernel(GemmArgs a, GemmTa
       for (; m >= 1; m >>= 1) total += __shfl_xor(total, m, kWave);
       constexpr int LPP = CPR / NPASS;                      // lanes per pass
       const int64_t t = m0 + (cc / LPP) * RPP + rr;
-      if ((cc % LPP) == 0 && t < a.M) qo.rt_part[static_cast<int64_t>(tn) * a.M + t] = total;
+      if ((cc % LPP) == 0 && t < a.M) qo.rt_part[static_cast<int64_t>(slot0 + tn) * a.M + t] = total;
     }
   }
+}
+
+template <int BITS, int WGM, int WGN, int WM, int WN, bool PARTIALS, int OUT, bool CWISE>
+__global__ void __launch_bounds__(256, 2) cluster_gemm_kernel(GemmArgs a, GemmTab tab, GemmQuantOut qo) {
+  gemm_tile<BITS, WGM, WGN, WM, WN, PARTIALS, OUT, CWISE>(a, tab, qo, blockIdx.x, a.tiles_n, 0, 0);
+}
+
+// 64 x 256 tiles, and behind them 64 x 128 tiles on the columns from 256 * tiles_n on (tail_n columns of tiles).
+template <int BITS, int OUT, bool CWISE>
+__global__ void __launch_bounds__(256, 2) cluster_gemm_large_kernel(GemmArgs a, GemmTab tab, GemmQuantOut qo) {
+  const int large = a.tiles_m * a.tiles_n;
+  if (static_cast<int>(blockIdx.x) < large)
+    gemm_tile<BITS, 1, 4, 2, 2, false, OUT, CWISE>(a, tab, qo, blockIdx.x, a.tiles_n, 0, 0);
+  else
+    gemm_tile<BITS, 1, 4, 2, 1, false, OUT, CWISE>(a, tab, qo, blockIdx.x - large, a.tail_n, a.tiles_n * 256, a.tiles_n);
 }
 
 // Sum over the column tiles of the row sums the quantizing output stage left: 16 rows per workgroup, 16
@@ -682,11 +700,31 @@ static constexpr size_t gemm_lds_bytes() {
   return front + terms + ((front - pipe >= cw_bytes) ? 0 : cw_bytes);
 }
 
-template <int BITS, int WGM, int WGN, int WM, int WN, bool PARTIALS, int OUT, bool CWISE>
-static int32_t raise_lds_limit(hipStream_t st) {
-  static LdsGrant lds_granted;
-  return ensure_dynamic_lds(reinterpret_cast<const void*>(cluster_gemm_kernel<BITS, WGM, WGN, WM, WN, PARTIALS, OUT, CWISE>),
-                            gemm_lds_bytes<WGM * WM * 32, WGN * WN * 32, PARTIALS, CWISE>(), &lds_granted, st);
+// Fills in the number of tiles; tile order inside an XCD's range: blocks of 32 (16) row tiles x 4 column tiles (measured best of
+// the shapes from 4 x 16 to 128 x 2 on the 8192 x 49152 x 12288 product, 1 % over 16 x 4, 5 % over 4 x 16)
+static GemmArgs tiled(const GemmArgs& a, int bm, int bn) {
+  GemmArgs b = a;
+  b.tiles_n = (a.N + bn - 1) / bn;
+  b.tail_n = 0;
+  b.tiles_m = static_cast<int32_t>((a.M + bm - 1) / bm);
+  b.grp_m = (b.tiles_m % 32 == 0) ? 32 : ((b.tiles_m % 16 == 0) ? 16 : 0);
+  b.grp_n = 4;
+  return b;
+}
+
+template <typename Kernel>
+static int32_t launch_tiles(Kernel kern, size_t shmem, const GemmArgs& b, const GemmTab& tab, const GemmQuantOut& qo, bool sums,
+                            float* q_rowterm, hipStream_t st) {
+  const int32_t cols = b.tiles_n + b.tail_n;
+  const dim3 grid(static_cast<unsigned>(cols) * static_cast<unsigned>(b.tiles_m));
+  hipLaunchKernelGGL(kern, grid, dim3(256), shmem, st, b, tab, qo);
+  RPTQ_HIP(hipGetLastError());
+  if (sums) {
+    hipLaunchKernelGGL(rowterm_reduce_kernel, dim3(static_cast<unsigned>((b.M + 15) / 16)), dim3(256), 0, st,
+                       qo.rt_part, cols, b.M, q_rowterm);
+    RPTQ_HIP(hipGetLastError());
+  }
+  return RPTQ_OK;
 }
 
 template <int BITS, int WGM, int WGN, int WM, int WN, bool PARTIALS, int OUT, bool CWISE>
@@ -694,23 +732,27 @@ static int32_t launch_cfg(const GemmArgs& a, const GemmTab& tab, const GemmQuant
   constexpr int BM = WGM * WM * 32, BN = WGN * WN * 32;
   constexpr size_t shmem = gemm_lds_bytes<BM, BN, PARTIALS, CWISE>();
   auto kern = cluster_gemm_kernel<BITS, WGM, WGN, WM, WN, PARTIALS, OUT, CWISE>;
-  if (int32_t st_lds = raise_lds_limit<BITS, WGM, WGN, WM, WN, PARTIALS, OUT, CWISE>(st)) return st_lds;
-  GemmArgs b = a;
-  b.tiles_n = (a.N + BN - 1) / BN;
-  b.tiles_m = static_cast<int32_t>((a.M + BM - 1) / BM);
-  // tile order inside an XCD's range: blocks of 32 (16) row tiles x 4 column tiles (measured best of the
-  // shapes from 4 x 16 to 128 x 2 on the 8192 x 49152 x 12288 product, 1 % over 16 x 4, 5 % over 4 x 16)
-  b.grp_m = (b.tiles_m % 32 == 0) ? 32 : ((b.tiles_m % 16 == 0) ? 16 : 0);
-  b.grp_n = 4;
-  const dim3 grid(static_cast<unsigned>(b.tiles_n) * static_cast<unsigned>(b.tiles_m));
-  hipLaunchKernelGGL(kern, grid, dim3(256), shmem, st, b, tab, qo);
-  RPTQ_HIP(hipGetLastError());
-  if (OUT >= 2) {
-    hipLaunchKernelGGL(rowterm_reduce_kernel, dim3(static_cast<unsigned>((a.M + 15) / 16)), dim3(256), 0, st,
-                       qo.rt_part, b.tiles_n, a.M, q_rowterm);
-    RPTQ_HIP(hipGetLastError());
+  static LdsGrant lds_granted;
+  if (int32_t s = ensure_dynamic_lds(reinterpret_cast<const void*>(kern), shmem, &lds_granted, st)) return s;
+  return launch_tiles(kern, shmem, tiled(a, BM, BN), tab, qo, OUT >= 2, q_rowterm, st);
+}
+
+// 64 x 256 tiles, the last tail_cols columns of them as 64 x 128 tiles; `launch` false: only the LDS limit is raised
+template <int BITS, int OUT, bool CWISE>
+static int32_t launch_large(const GemmArgs& a, const GemmTab& tab, const GemmQuantOut& qo, float* q_rowterm, int tail_cols,
+                            hipStream_t st, bool launch = true) {
+  constexpr size_t large = gemm_lds_bytes<64, 256, false, CWISE>(), small = gemm_lds_bytes<64, 128, false, CWISE>();
+  constexpr size_t shmem = large > small ? large : small;
+  auto kern = cluster_gemm_large_kernel<BITS, OUT, CWISE>;
+  static LdsGrant lds_granted;
+  if (int32_t s = ensure_dynamic_lds(reinterpret_cast<const void*>(kern), shmem, &lds_granted, st)) return s;
+  if (!launch) return RPTQ_OK;
+  GemmArgs b = tiled(a, 64, 256);
+  if (tail_cols > 0) {
+    b.tiles_n -= tail_cols;
+    b.tail_n = (a.N - b.tiles_n * 256 + 127) / 128;
   }
-  return RPTQ_OK;
+  return launch_tiles(kern, shmem, b, tab, qo, OUT >= 2, q_rowterm, st);
 }
 
 // The 32 x 128 tile beyond 32 tokens.  With larger tiles part of the chip idles and a wave has no other to run beside; with
@@ -746,8 +788,8 @@ template <int BITS, bool PARTIALS, int OUT, bool CWISE = false>
 static int32_t launch_shape(const GemmArgs& a, const GemmTab& tab, const GemmQuantOut& qo, float* q_rowterm, hipStream_t st) {
   // Every call of more than 32 rows raises the limit of the 64 x 256 tile, whichever kernel serves it: a program that ran
   // one such call may record any other.
-  if (!PARTIALS && a.M > 32) {
-    const int32_t s = raise_lds_limit<BITS, 1, 4, 2, 2, PARTIALS, OUT, CWISE>(st);
+  if constexpr (!PARTIALS) if (a.M > 32) {
+    const int32_t s = launch_large<BITS, OUT, CWISE>(a, tab, qo, q_rowterm, 0, st, false);
     if (s && s != RPTQ_ERR_CAPTURE) return s;               // (while recording: the launch below tells if it needs it)
   }
   if constexpr (!PARTIALS && !CWISE && (OUT == kOutBf16 || OUT == kOutF32)) {
@@ -769,10 +811,25 @@ static int32_t launch_shape(const GemmArgs& a, const GemmTab& tab, const GemmQua
   // (The sums and their order are the same.)
   constexpr int64_t kRound = 512;
   const int64_t tiles = (a.M + 63) / 64 * ((a.N + 255) / 256);
+  // Tiles beyond a whole number per compute unit (256 of them) leave most of the chip idle at the end; where they are 128 or
+  // fewer, their columns go out as 64 x 128 tiles, one per compute unit at most, in the same launch.  (More than that, cut in
+  // two, come to two small tiles on some compute units: 199 beyond 125 | 125 us, 256 beyond 345 | 364 at K = 20480.)  us
+  // before | now, K = 5120 (* 2048), by the number of 64 x 256 tiles:
+  //   Y as bf16   576: 66 | 64   640: 66 | 64   1088: 121 | 111   1152*: 55.1 | 51.2   1408: 141 | 135
+  //   next site's codes   576: 68.3 | 67.7   640: 70.3 | 67.9   5248: 488 | 481
+  //   a pair per cluster (64 x 128 tiles up to 704 of these instead: 576: 78 | 82   640: 81 | 84)
+  if constexpr (!PARTIALS) {
+    const int64_t rows = (a.M + 63) / 64, over = tiles % (kRound / 2), cols = (over + rows - 1) / rows;
+    if (tiles > (CWISE ? kRound * 11 / 8 : kRound) && over > 0 && 2 * cols * rows <= kRound / 2)
+      return launch_large<BITS, OUT, CWISE>(a, tab, qo, q_rowterm, static_cast<int>(cols), st);
+  }
   if constexpr (!PARTIALS)
     if (tiles <= kRound * 3 / 4 || (tiles > kRound && tiles <= kRound * 11 / 8))
       return launch_cfg<BITS, 1, 4, 2, 1, PARTIALS, OUT, CWISE>(a, tab, qo, q_rowterm, st);
-  return launch_cfg<BITS, 1, 4, 2, 2, PARTIALS, OUT, CWISE>(a, tab, qo, q_rowterm, st);
+  if constexpr (PARTIALS)
+    return launch_cfg<BITS, 1, 4, 2, 2, PARTIALS, OUT, CWISE>(a, tab, qo, q_rowterm, st);
+  else
+    return launch_large<BITS, OUT, CWISE>(a, tab, qo, q_rowterm, 0, st);
 }
 
 // out_mode: -1 partial sums, kOutBf16, kOutF32, or the next site's code bits (3, 4, 8)
