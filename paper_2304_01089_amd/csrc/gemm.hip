@@ -820,8 +820,10 @@ static int32_t launch_shape(const GemmArgs& a, const GemmTab& tab, const GemmQua
   //   a pair per cluster (64 x 128 tiles up to 704 of these instead: 576: 78 | 82   640: 81 | 84)
   if constexpr (!PARTIALS) {
     const int64_t rows = (a.M + 63) / 64, over = tiles % (kRound / 2), cols = (over + rows - 1) / rows;
-    if (tiles > (CWISE ? kRound * 11 / 8 : kRound) && over > 0 && 2 * cols * rows <= kRound / 2)
-      return launch_large<BITS, OUT, CWISE>(a, tab, qo, q_rowterm, static_cast<int>(cols), st);
+    if (tiles > (CWISE ? kRound * 11 / 8 : kRound) && over > 0 && 2 * cols * rows <= kRound / 2) {
+      const int32_t s = launch_large<BITS, OUT, CWISE>(a, tab, qo, q_rowterm, static_cast<int>(cols), st);
+      if (s != RPTQ_ERR_CAPTURE) return s;                  // (recorded before its LDS limit was raised: tiles that need none, below)
+    }
   }
   if constexpr (!PARTIALS)
     if (tiles <= kRound * 3 / 4 || (tiles > kRound && tiles <= kRound * 11 / 8))

@@ -66,3 +66,12 @@ print("ok")
 def test_record_without_the_same_call_before(what):
     r = subprocess.run([sys.executable, "-u", "-c", PROGRAM, what], cwd=ROOT, capture_output=True, text=True, timeout=100)
     assert r.returncode == 0 and r.stdout.strip().endswith("ok"), r.stdout + r.stderr
+
+
+@pytest.mark.parametrize("what", ["bf16", "f32", "quant"])
+def test_record_the_first_product_of_a_process(what):
+    """525 tiles of 64 x 256 (and 550 of the padded next site), 8-bit codes, K = 5120: where no call has raised the LDS limit of
+    that tile, smaller ones serve a product of one to 1.4 rounds of it."""
+    program = PROGRAM.replace("1024, 5376, 16, 4", "5120, 5376, 16, 8").replace("(40, (2900, 1500, 300, 33))", "(None, (1600,))")
+    r = subprocess.run([sys.executable, "-u", "-c", program, what], cwd=ROOT, capture_output=True, text=True, timeout=100)
+    assert r.returncode == 0 and r.stdout.strip().endswith("ok") and "recorded %s 1600" % what in r.stdout, r.stdout + r.stderr
