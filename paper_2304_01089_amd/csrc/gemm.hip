@@ -21,6 +21,7 @@
 #include "device_common.h"
 #include "rptq_internal.h"
 #include "gemm_common.h"
+#include "launch_rules.h"
 
 namespace rptq {
 
@@ -788,8 +789,8 @@ template <int BITS, bool PARTIALS, int OUT, bool CWISE = false>
 static int32_t launch_shape(const GemmArgs& a, const GemmTab& tab, const GemmQuantOut& qo, float* q_rowterm, hipStream_t st) {
   // Every call of more than 32 rows raises the limit of the 64 x 256 tile, whichever kernel serves it: a program that ran
   // one such call may record any other.
-  if constexpr (!PARTIALS) if (a.M > 32) {
-    const int32_t s = launch_large<BITS, OUT, CWISE>(a, tab, qo, q_rowterm, 0, st, false);
+  if constexpr (!PARTIALS) {
+    const int32_t s = a.M > 32 ? launch_large<BITS, OUT, CWISE>(a, tab, qo, q_rowterm, 0, st, false) : RPTQ_OK;
     if (s && s != RPTQ_ERR_CAPTURE) return s;               // (while recording: the launch below tells if it needs it)
   }
   if constexpr (!PARTIALS && !CWISE && (OUT == kOutBf16 || OUT == kOutF32)) {
@@ -803,25 +804,22 @@ static int32_t launch_shape(const GemmArgs& a, const GemmTab& tab, const GemmQua
   // weight fragment feeds two MFMAs and no two waves expand the same weights.  Two such workgroups fill a compute unit,
   // 512 the chip.  A 64 x 128 tile (half the accumulators, three workgroups per compute unit: 768, or 384 of the large
   // tiles, fill the chip) stages the activations twice as often; it is taken where it needs one round for fewer than
-  // 512 tiles, and where the second round of large tiles is well short of full.  us for 64 x 256 | 64 x 128 at K = 5120
-  // (* 3000), by the number of 64 x 256 tiles:
-  //   Y as bf16            352: 51 | 43   384: 50 | 45   416: 52 | 60   576*: 60 | 53   640: 80 | 74    768: 89 | 87
-  //   next site's codes    335: 60 | 53   375: 62 | 56   416: 54 | 63   496: 57 | 66   624*: 66 | 57   656: 85 | 86   864: 103 | 109
-  //   a pair per cluster   320: 65 | 52   384: 64 | 54   416: 66 | 73   576*: 89 | 67   640: 108 | 89   768: 111 | 106
-  // (The sums and their order are the same.)
+  // 512 tiles, and where the second round of large tiles is well short of full.  Medians in us, 64 x 256 | 64 x 128, 4 bits,
+  // K = 5120 (* 3008), by rows x columns (64 x 256 tiles):
+  //                        Y as bf16                  next site's codes          a pair per cluster
+  //   1408 x 4096 (352)    43.6 | 38.7  31.4 | 27.6*   46.1 | 42.9  34.3 | 30.7*   56.0 | 46.8  39.0 | 32.7*
+  //   2048 x 3072 (384)    42.3 | 39.5  29.3 | 26.7*   46.6 | 44.0  32.8 | 30.3*   56.3 | 47.9  37.2 | 32.1*
+  //   1664 x 4096 (416)    43.2 | 51.1  28.9 | 33.5*   47.5 | 57.3  32.6 | 39.1*   58.4 | 64.8  38.4 | 42.3*
+  //   2624 x 4096 (656)    72.0 | 71.0  44.8 | 44.3*   78.0 | 76.9  52.1 | 50.3*   96.4 | 84.4  60.8 | 54.6*
+  //   2112 x 5120 (660)    71.5 | 70.8  45.5 | 44.5*   79.2 | 77.3  52.9 | 50.6*   96.1 | 84.7  61.0 | 54.7*
+  //   2048 x 6144 (768)    77.8 | 75.9  46.6 | 46.6*   79.0 | 79.9  52.8 | 52.2*   95.6 | 88.3  60.6 | 56.9*
+  // Some counts above 512 run both in one launch (gemm_tail_columns).  The sums and their order are the same; a row's term for
+  // the next site is rounded once from fp64 sums per column tile, so it may differ in its last place.
   constexpr int64_t kRound = 512;
   const int64_t tiles = (a.M + 63) / 64 * ((a.N + 255) / 256);
-  // Tiles beyond a whole number per compute unit (256 of them) leave most of the chip idle at the end; where they are 128 or
-  // fewer, their columns go out as 64 x 128 tiles, one per compute unit at most, in the same launch.  (More than that, cut in
-  // two, come to two small tiles on some compute units: 199 beyond 125 | 125 us, 256 beyond 345 | 364 at K = 20480.)  us
-  // before | now, K = 5120 (* 2048), by the number of 64 x 256 tiles:
-  //   Y as bf16   576: 66 | 64   640: 66 | 64   1088: 121 | 111   1152*: 55.1 | 51.2   1408: 141 | 135
-  //   next site's codes   576: 68.3 | 67.7   640: 70.3 | 67.9   5248: 488 | 481
-  //   a pair per cluster (64 x 128 tiles up to 704 of these instead: 576: 78 | 82   640: 81 | 84)
   if constexpr (!PARTIALS) {
-    const int64_t rows = (a.M + 63) / 64, over = tiles % (kRound / 2), cols = (over + rows - 1) / rows;
-    if (tiles > (CWISE ? kRound * 11 / 8 : kRound) && over > 0 && 2 * cols * rows <= kRound / 2) {
-      const int32_t s = launch_large<BITS, OUT, CWISE>(a, tab, qo, q_rowterm, static_cast<int>(cols), st);
+    if (const int cols = gemm_tail_columns(a.M, a.N, a.slices, BITS, CWISE)) {
+      const int32_t s = launch_large<BITS, OUT, CWISE>(a, tab, qo, q_rowterm, cols, st);
       if (s != RPTQ_ERR_CAPTURE) return s;                  // (recorded before its LDS limit was raised: tiles that need none, below)
     }
   }

@@ -53,7 +53,7 @@ struct GemmTab {
 // n of the next site's cluster-order layout).  Passed by value; unused by the other kernels.
 struct GemmQuantOut {
   uint8_t* codes;                          // packed codes of the next site, [M, N * bits / 8]
-  double* rt_part;                         // [tiles_n, M]: per column tile, the de-quantized row sum
+  double* rt_part;                         // [tiles_n + tail_n, M]: per column tile, the de-quantized row sum
   int32_t row_bytes;                       // N * bits / 8
   int32_t relu;
   int32_t g;
