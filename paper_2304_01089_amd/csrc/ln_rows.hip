@@ -12,6 +12,7 @@
 #include <hip/hip_runtime.h>
 
 #include "device_common.h"
+#include "launch_rules.h"
 #include "ln_common.h"
 #include "rptq_internal.h"
 
@@ -294,31 +295,9 @@ static int32_t launch_rows_cfg(const LnQuantArgs& a, const LnRowsTab& tab, int n
   return ln ? launch_rows_count<BITS, NUNIT, 2, true>(a, tab, rows, threads, st) : launch_rows_count<BITS, NUNIT, 2, false>(a, tab, rows, threads, st);
 }
 
-// Rows of a workgroup, R.  A workgroup takes its time in a chain of waits, so one row each is fastest while the workgroups of a
-// compute unit run side by side; then two and four, which share the per-position constants (12 bytes a code against the row's
-// 2; eight measured no better).  The lines, in waves per compute unit at one row each (L), us in a recorded graph with one |
-// two | four rows, rows from memory:
-//      LayerNorm, 4 bits                    3 bits                                  4 bits, without LayerNorm
-//      500 x 2048 (L 10)  4.4 | 4.8 | 5.7    700 x 1536 (L  5)  5.7 |  6.2 |  6.6    700 x 2048 (L 14)  4.1 | 4.3 | 4.4
-//     1000 x 1536 (L 16)  4.9 | 5.1 | 5.6   1500 x 1536 (L 12)  7.6 |  6.6 |  8.4   1000 x 2048 (L 20)  4.5 | 4.5 | 4.6
-//     1000 x 2048 (L 20)  5.7 | 5.8 | 6.0   1000 x 3000 (L 16)  8.8 |  7.5 |  7.9   1500 x 2048 (L 29)  5.6 | 5.2 | 5.6
-//     1500 x 2048 (L 29)  7.1 | 6.8 | 7.5   1500 x 3000 (L 23) 11.8 |  9.3 | 10.1   1500 x 3000 (L 41)  6.8 | 6.1 | 6.6
-//     2000 x 2048 (L 39)  8.8 | 8.1 | 8.3   2000 x 3000 (L 31) 13.5 | 10.3 | 10.3   3000 x 2048 (L 59)  8.5 | 7.2 | 7.1
-//     2000 x 3000 (L 55) 11.3 | 9.8 | 9.2    300 x 2048 (L  4)  5.5 |  5.1 |  6.7    at 3 bits 1000 x 2048 (L 12) 5.0 | 5.2 | 5.5
-// (at 3 bits a thread holds sixteen codes' constants, so that sharing them pays sooner; in rows of more than eight waves the
-// constants count as much: 512 x 5120 6.3 | 6.2).
-static int rows_per_workgroup(int64_t M, int waves, int cus, int bits, bool ln) {
-  const int64_t at_one = M * waves;                          // waves, at one row each
-  const int one = bits > 3 ? (ln ? 24 : 20) : (ln ? 8 : 12), two = bits > 3 ? 44 : (ln ? 24 : 40);
-  if (M <= cus || waves == 1) return 1;
-  if (waves <= (bits == 3 && ln ? 2 : 8) && at_one <= static_cast<int64_t>(one) * cus) return 1;
-  if (M <= 2 * static_cast<int64_t>(cus) || waves < 4 || (waves <= 8 && at_one <= static_cast<int64_t>(two) * cus)) return 2;
-  return 4;
-}
-
-// Which calls come here.  With more rows the pipelined kernel catches up, the sooner the wider the row and the fewer waves hold it (a row's parts take 16 bytes of LDS per thread,
-// so fewer rows are resident; at 3 bits a row has half the waves).  us in a recorded graph, pipelined | this kernel,
-// 4 bits (or as stated):
+// Which calls come here.  With many rows per compute unit the pipelined kernel catches up, the sooner the wider the row and the
+// fewer waves hold it (a row's parts take 16 bytes of LDS per thread, so fewer rows are resident; at 3 bits a row has half the
+// waves).  us in a recorded graph, pipelined | this kernel, 4 bits (or as stated):
 //                       LayerNorm       without                            LayerNorm       without
 //     1 x  2048          4.4 |  2.9     3.0 |  2.2      2048 x  768        6.1 |  4.5     4.3 |  3.3
 //   128 x   768 (8)      3.8 |  3.0     2.8 |  2.5      2048 x  768 (3)    6.7 |  5.5     4.1 |  3.8
@@ -347,9 +326,7 @@ int32_t launch_ln_rows(const LnQuantArgs& a, const ClusterGeom& geom, const Quan
   else if (a.d <= 2048) most = ln ? 64 : (a.d <= 640 ? 32 : (a.d <= 1792 ? 64 : 128));
   else most = a.d <= (bits == 4 ? 4096 : 3072) ? 32 : (a.d <= 5120 ? 16 : 4);
   if (a.M > static_cast<int64_t>(cus) * most) return RPTQ_OK;
-  // (a wave adds one row up, so there are no more rows than waves)
-  const int waves = threads / kWave;
-  const int rows = rows_per_workgroup(a.M, waves, cus, bits, ln);
+  const int rows = ln_rows_per_workgroup(a.M, threads / kWave, nunit, cus, bits, ln);
   LnRowsTab tab;
   for (int i = 0; i < RPTQ_MAX_CLUSTERS; ++i) {
     tab.pad_off[i] = i < geom.g ? geom.pad_off[i] : INT32_MAX;

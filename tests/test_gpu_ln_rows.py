@@ -68,16 +68,15 @@ def test_few_rows_equal_many(d, g, bits, ln):
 
 @pytest.mark.parametrize("ln", [True, False])
 @pytest.mark.parametrize("bits", [3, 4, 8])
-@pytest.mark.parametrize("d,g", [(776, 8), (1536, 7), (2048, 16), (4072, 32), (5120, 32)])
+@pytest.mark.parametrize("d,g", [(776, 8), (1536, 7), (2048, 16), (2560, 8), (4072, 32), (5120, 32), (8064, 4)])
 def test_rows_of_a_workgroup(d, g, bits, ln):
-    """One, two or four rows in a workgroup: either side of every line of that rule (waves per compute unit at one row each)."""
+    """One, two or four rows in a workgroup: either side of every line of that rule (rows per compute unit)."""
     import paper_2304_01089_amd as rp
     cus = rp.rptq_device_info()["compute_units"]
-    call = make_call(d, g, bits, cus * 16, ln=ln)
-    codes, rowterm = call(cus * 16)
-    waves = -(-(codes.shape[1] * 8 // bits // (16 if bits == 3 else 8)) // 64)
-    lines = (cus * line // waves + k for line in (8, 12, 20, 24, 40, 44) for k in (0, 1))
-    for m in sorted({m for m in lines if m <= cus * 16}):
+    most = min(12, rows_per_unit(d, bits, ln))
+    call = make_call(d, g, bits, cus * most, ln=ln)
+    codes, rowterm = call(cus * most)
+    for m in (cus * line + k for line in range(1, most) for k in (-1, 0, 1)):
         c, r = call(m)
         assert torch.equal(c, codes[:m]) and torch.equal(r, rowterm[:m]), m
 
