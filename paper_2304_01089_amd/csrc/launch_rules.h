@@ -19,7 +19,7 @@ namespace rptq {
 //         2048 x  8704              41 |  38     64 |  59      118 | 108      220 | 203
 //   a pair per cluster
 //         2048 x  8704              47 |  43     78 |  70      146 | 130      240 | 221
-// (4 bits; 3 and 8 bits gain as much; of 1000 points beyond 704 tiles the worst was even.)  From 513 to 704 tiles what competes is
+// (4 bits; 3 and 8 bits gain as much; of 1290 points beyond 704 tiles the worst was even.)  From 513 to 704 tiles what competes is
 // 64 x 128 tiles throughout, and these are ahead but for 8-bit codes over a long K: 64 x 128 tiles | with the small ones behind:
 //                                   K = 768        2048         5120          12288
 //   Y     2048 x 4608 (576, 64)    20.0 | 21.0  31.4 | 32.6  59.7 | 60.5  119.5 | 118.3
